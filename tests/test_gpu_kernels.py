@@ -179,6 +179,45 @@ def test_attention_ragged(torch_cuda, lengths, H, dh, prec, prop):
     print(f"  max |dO| = {worst:.3e}")
 
 
+
+@pytest.mark.parametrize("lengths,H,dh", [
+    ([64, 65, 1, 16, 17, 128], 2, 64),    # chunk and query-block edges
+    ([256, 255, 63, 193], 3, 20),         # head padded from 20 to 32 dims
+    ([257, 640, 2, 320], 1, 128),         # longest samples, widest heads
+    ([130, 66], 2, 36),                   # padded from 36 to 64 dims
+    ([40, 3], 2, 6),                      # width without 16-byte pieces: general kernel
+    ([50, 7], 1, 132),                    # wider than the matrix kernel takes
+])
+def test_attention_fp32_widths(torch_cuda, lengths, H, dh):
+    """fp32 attention over head widths, sample lengths and (shifted by one
+    float) unaligned buffers: every form against float64.  E and the two
+    products are fp32 sums of at most max(T, dh) terms."""
+    torch = torch_cuda
+    print(f"[attention fp32] T={lengths} H={H} dh={dh}", flush=True)
+    rng = np.random.default_rng(sum(lengths) + dh)
+    cu = _offsets(lengths)
+    M, d = int(cu[-1]), H * dh
+    qkv = rng.standard_normal((M, 3 * d)).astype(np.float32)
+    size = rng.integers(1, 5, size=M).astype(np.float32)
+    base = torch.zeros(M * 3 * d + 1, device="cuda")
+    for shift in (0, 1):
+        dq = base[shift:shift + M * 3 * d].view(M, 3 * d)
+        dq.copy_(torch.from_numpy(qkv))
+        out, cls = _kern().attention(dq, torch.from_numpy(size).cuda(), cu, H, True,
+                                     cls_tmax=max(lengths))
+        out, cls = out.cpu().numpy(), cls.cpu().numpy()
+        for i, T in enumerate(lengths):
+            q, k, v = (qkv[cu[i]:cu[i + 1], j * d:(j + 1) * d].astype(np.float64)
+                       .reshape(T, H, dh).transpose(1, 0, 2) for j in range(3))
+            S = q @ k.transpose(0, 2, 1) / np.sqrt(dh) + np.log(size[cu[i]:cu[i + 1]])
+            P = np.exp(S - S.max(-1, keepdims=True))
+            P /= P.sum(-1, keepdims=True)
+            want = (P @ v).transpose(1, 0, 2).reshape(T, d)
+            tol = 2.0 ** -24 * max(T, dh) * 4
+            assert np.abs(out[cu[i]:cu[i + 1]] - want).max() <= tol * np.abs(v).max(), (shift, i)
+            assert np.abs(cls[i, :, :T] - P[:, 0]).max() <= tol, (shift, i)
+            assert (cls[i, :, T:] == -1).all()
+
 # ----------------------------------------------------------------- merge --
 def _tokens(rng, T, d, rank=8):
     """Hidden states with a low-rank structure (cosines spread over [-1, 1])."""
