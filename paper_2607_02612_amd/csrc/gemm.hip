@@ -2,7 +2,9 @@
 // residual add into the fp32 stream, patch-embedding scatter, fp32 logits).
 //
 // bf16 path: MFMA v_mfma_f32_32x32x16_bf16 on 128x128 tiles staged through
-// LDS, fp32 accumulation.  fp32 path: LDS-tiled VALU FMA (no rounding).
+// LDS, fp32 accumulation.  fp32 path (no rounding): MFMA
+// v_mfma_f32_16x16x4_f32, or LDS-tiled VALU FMA where the operands do not
+// have its form.
 // Rows are the packed live tokens of all samples, so ragged lengths are
 // invisible here: M is read from the device counters and the grid is sized
 // for an upper bound (tiles past M return at once).
@@ -14,6 +16,7 @@ namespace fusion {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 template <typename T>
 __device__ __forceinline__ void epilogue(const Epi& e, int r, int n, float acc) {
@@ -146,6 +149,7 @@ __global__ __launch_bounds__(256) void gemm_valu(const T* __restrict__ A,
 constexpr int NB = 128;
 constexpr int NXCD = 8;
 constexpr long THIN_TILES = 768;
+constexpr long F32_TILES64 = 512;
 
 // 16-byte chunk c of staged row r (64-byte rows: four chunks)
 __device__ __forceinline__ int kslot(int r, int c) { return c ^ ((r >> 2) & 3); }
@@ -505,11 +509,162 @@ __global__ __launch_bounds__(MB / (32 * WR) * 128, MB == 128 ? 3 : 1) void gemm_
 }
 
 
+// ------------------------------------------------------------ fp32 MFMA --
+// MB x MB output tile per workgroup, 4 waves in a 2 x 2 grid, each wave
+// (MB / 32)^2 blocks of v_mfma_f32_16x16x4_f32.  K is consumed 16 floats at a
+// time (64-byte rows, the bf16 kernel's staged layout and chunk permutation)
+// through a ring of NSTG stages filled by the asynchronous global -> LDS path.
+// A lane's 16-byte piece of a staged row feeds four MFMA steps: slot g = l /
+// 16 of step i is k = 16 kt + 4 g + i, in this order for every tile size, so
+// a row's result does not depend on the tile.  Large products are bound by
+// the fp32 matrix rate (50432 x 1536 x 384 with 64-row tiles: 500 us, 119 of
+// the nominal 157 TFLOP/s; 128-row tiles measured 508 us and lost more below
+// that), small ones by the latency of the first stages (1573 x 1152 x 384:
+// 21 us against 62 us for the general kernel).  The product is transposed (W
+// as the row operand): lane (g, c) holds row m = .. + c, columns n = .. + 4 g
+// + q.
+template <int MB, int NSTG>
+__global__ __launch_bounds__(256) void gemm_mfma_f32(const float* __restrict__ A, int lda,
+                                                     const float* __restrict__ W, int N, int K,
+                                                     const int* M_dev, int M_host, int n_mt,
+                                                     int vec, Epi e) {
+  constexpr int ROWB = 64, KS = 16;
+  constexpr int WB = MB / 2, NW = WB / 16;       // wave tile rows, 16-row blocks
+  constexpr int STGB = 2 * MB * ROWB;            // bytes per stage: A rows, W rows
+  constexpr int DPW = 2 * MB / 16 / 4;           // DMA instructions per wave and stage
+  const int M = M_dev ? *M_dev : M_host;
+  const int n_nt = (N + MB - 1) / MB;
+  const int id = blockIdx.x;
+  const int xcd = id % NXCD, local = id / NXCD;
+  const int mt = (local / n_nt) * NXCD + xcd, nt = local % n_nt;
+  const int m0 = mt * MB, n0 = nt * MB;
+  if (mt >= n_mt || m0 >= M) return;
+  __shared__ __attribute__((aligned(16))) char smem[NSTG * STGB];
+  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int wm = wave >> 1, wn = wave & 1, g = lane >> 4, c = lane & 15;
+
+  const float* sbase[DPW];
+  unsigned voff[DPW], dst[DPW];
+#pragma unroll
+  for (int u = 0; u < DPW; u++) {
+    const int q = wave * DPW + u;  // 16-row block: A rows first, then W rows
+    const bool isA = q < MB / 16;
+    const int r = (isA ? q : q - MB / 16) * 16 + lane / 4;
+    const int gr = isA ? min(m0 + r, M - 1) : min(n0 + r, N - 1);
+    sbase[u] = isA ? A : W;
+    voff[u] = (unsigned)(((size_t)gr * (isA ? lda : K) + kslot(r, lane % 4) * 4) * 4);
+    dst[u] = q * 16 * ROWB;
+  }
+  const int nk = K / KS;
+#pragma unroll
+  for (int st = 0; st < NSTG - 1; st++)
+    if (st < nk) {
+#pragma unroll
+      for (int u = 0; u < DPW; u++) dma16s(sbase[u] + st * KS, voff[u], lds0 + st * STGB + dst[u]);
+    }
+  f32x4_t acc[NW][NW];
+#pragma unroll
+  for (int i = 0; i < NW; i++)
+#pragma unroll
+    for (int j = 0; j < NW; j++) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  int st = 0, sn = NSTG - 1;  // ring slots of step kt and of step kt + NSTG - 1
+  for (int kt = 0; kt < nk; kt++) {
+    if (kt + NSTG - 2 < nk)
+      wait_vm<DPW * (NSTG - 2)>();
+    else
+      wait_vm<0>();
+    __syncthreads();
+    if (kt + NSTG - 1 < nk) {
+#pragma unroll
+      for (int u = 0; u < DPW; u++)
+        dma16s(sbase[u] + (kt + NSTG - 1) * KS, voff[u], lds0 + sn * STGB + dst[u]);
+    }
+    const char* Ab = smem + st * STGB;
+    const char* Bb = Ab + MB * ROWB;
+    f32x4_t av[NW], bv[NW];
+#pragma unroll
+    for (int i = 0; i < NW; i++) {
+      const int ra = wm * WB + i * 16 + c, rb = wn * WB + i * 16 + c;
+      av[i] = *(const f32x4_t*)(Ab + ra * ROWB + (kslot(ra, g) << 4));
+      bv[i] = *(const f32x4_t*)(Bb + rb * ROWB + (kslot(rb, g) << 4));
+    }
+#pragma unroll
+    for (int q = 0; q < 4; q++)
+#pragma unroll
+      for (int i = 0; i < NW; i++)
+#pragma unroll
+        for (int j = 0; j < NW; j++)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bv[j][q], av[i][q], acc[i][j], 0, 0, 0);
+    st = st + 1 == NSTG ? 0 : st + 1;
+    sn = sn + 1 == NSTG ? 0 : sn + 1;
+  }
+#pragma unroll
+  for (int i = 0; i < NW; i++) {
+    const int m = m0 + wm * WB + i * 16 + c;
+    if (m >= M) continue;
+    if (!vec) {  // rows or columns that 16-byte accesses do not fit
+#pragma unroll
+      for (int j = 0; j < NW; j++)
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+          const int n = n0 + wn * WB + j * 16 + 4 * g + q;
+          if (n < N) epilogue<float>(e, m, n, acc[i][j][q]);
+        }
+      continue;
+    }
+    size_t orow = (size_t)m, prow = 0;
+    if (e.mode == EPI_PATCH) {
+      const int s = m / e.n0;
+      prow = 1 + (m - s * e.n0);
+      orow = (size_t)s * (e.n0 + 1) + prow;
+    } else if (e.rows) {
+      orow = (size_t)e.rows[m];
+    }
+#pragma unroll
+    for (int j = 0; j < NW; j++) {
+      const int n = n0 + wn * WB + j * 16 + 4 * g;
+      if (n >= N) continue;
+      f32x4_t v = acc[i][j] + *(const f32x4_t*)(e.bias + n);
+      f32x4_t* po = (f32x4_t*)((float*)e.out + orow * e.ldo + n);
+      if (e.mode == EPI_GELU) {
+#pragma unroll
+        for (int q = 0; q < 4; q++) v[q] = gelu_erf(v[q]);
+      }
+      if (e.mode == EPI_RESID) v = *po + v;
+      if (e.mode == EPI_PATCH) v = v + *(const f32x4_t*)(e.pos + prow * e.ldo + n);
+      *po = v;
+    }
+  }
+}
+
 template <>
 hipError_t launch_gemm<float>(const float* A, int lda, const float* W, int N,
                               int K, const int* M_dev, int M_host, int M_ub,
                               const Epi& e, hipStream_t s) {
   if (M_ub <= 0) return hipSuccess;
+  // matrix cores: whole 16-float K steps, 16-byte aligned operand rows within
+  // 32-bit byte offsets; anything else takes the general kernel
+  if (K >= 16 && K % 16 == 0 && lda % 4 == 0 && ((uintptr_t)A | (uintptr_t)W) % 16 == 0 &&
+      (size_t)M_ub * lda * 4 <= 0xFFFFFFFFull && (size_t)N * K * 4 <= 0xFFFFFFFFull) {
+    const int vec = N % 4 == 0 && e.ldo % 4 == 0 &&
+                    ((uintptr_t)e.out | (uintptr_t)e.bias | (uintptr_t)e.pos) % 16 == 0;
+    auto tiles = [&](int mb) { return (long)((M_ub + mb - 1) / mb) * ((N + mb - 1) / mb); };
+    auto grid = [&](int mb) {
+      return ((M_ub + mb - 1) / mb + NXCD - 1) / NXCD * NXCD * ((N + mb - 1) / mb);
+    };
+    // 64-row tiles from two of them per CU on (6304 x 384 x 384, 594 tiles:
+    // 25.6 against 26.6 us with 32-row tiles), below that 32-row tiles, whose
+    // K steps wait for less and of which more run at once (1573 x 1152 x 384,
+    // 450 tiles: 21.1 against 24.0 us; 197 x 384 x 1536: 17.8 against 37.0)
+    if (tiles(64) >= F32_TILES64)
+      gemm_mfma_f32<64, 6><<<grid(64), 256, 0, s>>>(A, lda, W, N, K, M_dev, M_host,
+                                                    (M_ub + 63) / 64, vec, e);
+    else
+      gemm_mfma_f32<32, 8><<<grid(32), 256, 0, s>>>(A, lda, W, N, K, M_dev, M_host,
+                                                    (M_ub + 31) / 32, vec, e);
+    return hipGetLastError();
+  }
   dim3 grid((M_ub + 63) / 64, (N + 63) / 64);
   gemm_valu<float><<<grid, 256, 0, s>>>(A, lda, W, N, K, M_dev, M_host, e);
   return hipGetLastError();

@@ -133,6 +133,48 @@ def test_gemm_fp32(torch_cuda, M, N, K, epi):
     assert np.abs(g - want).max() <= 1e-4
 
 
+@pytest.mark.parametrize("M,N,K,epi,shift", [
+    (33, 68, 16, "store", 0),      # one K step, edges of 32-row tiles
+    (31, 36, 144, "resid", 0),     # more K steps than ring stages
+    (95, 70, 48, "gelu", 0),       # columns that 16-byte stores do not fit
+    (2100, 1025, 32, "f32", 0),    # 64-row tiles, scalar stores
+    (4200, 516, 80, "resid", 0),   # 64-row tiles with edges
+    (40, 64, 40, "store", 0),      # K not a multiple of 16: general kernel
+    (40, 64, 64, "store", 1),      # operands off 16-byte alignment: general kernel
+])
+def test_gemm_fp32_tiles(torch_cuda, M, N, K, epi, shift):
+    """Each route of the fp32 product against float64 (K rounded products and
+    sums), rows through a map, and a row alone equal to the same row in M."""
+    torch = torch_cuda
+    print(f"[gemm fp32] M={M} N={N} K={K} epi={epi} shift={shift}", flush=True)
+    rng = np.random.default_rng(M + N + K)
+    A = rng.standard_normal((M, K)).astype(np.float32)
+    W = rng.standard_normal((N, K)).astype(np.float32)
+    bias = rng.standard_normal(N).astype(np.float32)
+    dA = torch.zeros(M * K + shift, device="cuda")[shift:].view(M, K)
+    dA.copy_(torch.from_numpy(A))
+    dW, db = torch.from_numpy(W).cuda(), torch.from_numpy(bias).cuda()
+    mapped = epi in ("resid", "f32")
+    rows = rng.permutation(M + 3)[:M].astype(np.int32) if mapped else np.arange(M)
+    x0 = rng.standard_normal((M + 3 if mapped else M, N)).astype(np.float32)
+    out = torch.from_numpy(x0.copy()).cuda()
+    _kern().gemm(dA, dW, db, epi, out, torch.from_numpy(rows).cuda() if mapped else None)
+    g = out.cpu().numpy()
+    ref = A.astype(np.float64) @ W.astype(np.float64).T + bias
+    bound = (np.abs(A).astype(np.float64) @ np.abs(W).astype(np.float64).T + np.abs(bias)
+             + np.abs(x0[rows])) * (K + 4) * 2.0 ** -24 + 1e-6
+    want = fo.gelu(ref.astype(np.float32)) if epi == "gelu" else ref
+    if epi == "resid":
+        want = want + x0[rows]
+    assert (np.abs(g[rows] - want) <= 2 * bound).all()
+    if mapped:
+        rest = np.setdiff1d(np.arange(M + 3), rows)
+        assert np.array_equal(g[rest], x0[rest])
+    one = torch.from_numpy(x0[rows[M - 1]][None].copy()).cuda()
+    _kern().gemm(dA[M - 1:], dW, db, epi, one)
+    assert np.array_equal(one.cpu().numpy()[0], g[rows[M - 1]])
+
+
 # ------------------------------------------------------------- attention --
 ATT_CASES = [
     # lengths, heads, dh, precision, prop_attn
