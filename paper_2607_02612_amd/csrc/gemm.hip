@@ -150,6 +150,8 @@ constexpr int NB = 128;
 constexpr int NXCD = 8;
 constexpr long THIN_TILES = 768;
 constexpr long F32_TILES64 = 512;
+// 32 x 32 blocks up to which a bf16 launch takes the small-launch kernel
+constexpr long SMALL_TILES = 2048;
 
 // 16-byte chunk c of staged row r (64-byte rows: four chunks)
 __device__ __forceinline__ int kslot(int r, int c) { return c ^ ((r >> 2) & 3); }
@@ -509,6 +511,175 @@ __global__ __launch_bounds__(MB / (32 * WR) * 128, MB == 128 ? 3 : 1) void gemm_
 }
 
 
+// ----------------------------------------------- bf16 MFMA, small launches --
+// Launches whose tiles leave most CUs idle are bound by the latency of one
+// wave's chain: copies issued, stage waited for, operands read, MFMAs.  Here
+// each of WM x WN waves of a workgroup computes one 32 x 32 block, NWV >= WM
+// WN waves share the copies (one wave alone spends more cycles issuing them
+// than in its MFMAs: 197 x 384 x 1536 took 8.7 us with one wave and 6.9 with
+// three loading ones beside it), the ring holds NSTG K steps of 64, and the
+// next step's operands are read before the current step's MFMAs.  The blocks
+// accumulate the same 16-wide K pieces in the same order from the bias as the
+// large tiles, and the epilogue does the same arithmetic, so results are
+// bit-identical to theirs.  Staged rows are 128 bytes with their eight
+// 16-byte chunks XOR-permuted by row % 8.  Row-map entries and residual rows
+// are fetched right after the ring's first loads.  The blocks follow the
+// dispatch order (a panel walk per XCD would leave XCDs idle here).
+template <int EPI, int WM, int WN, int NSTG, int NWV = WM * WN>
+__global__ __launch_bounds__(64 * NWV) void gemm_mfma_bf16_small(
+    const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W, int N, int K,
+    const int* M_dev, int M_host, Epi e) {
+  constexpr int KS = 64, ROWB = 128, RPI = 8;  // K step, bytes per staged row, rows per DMA
+  constexpr int MB = 32 * WM, NBS = 32 * WN;
+  constexpr bool HELP = NWV > WM * WN;
+  constexpr int STGB = (MB + NBS) * ROWB;
+  constexpr int DPW = (MB + NBS) / RPI / NWV;  // DMA instructions per wave and stage
+  static_assert((MB + NBS) / RPI % NWV == 0, "stage split");
+  const int M = M_dev ? *M_dev : M_host;
+  const int n_nt = (N + NBS - 1) / NBS;
+  const int mt = blockIdx.x / n_nt, nt = blockIdx.x - mt * n_nt;
+  const int m0 = mt * MB, n0 = nt * NBS;
+  if (m0 >= M) return;
+  __shared__ __attribute__((aligned(16))) char smem[NSTG * STGB];
+  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const bool mm = !HELP || wave < WM * WN;
+  const int wm = mm ? wave / WN : 0, wn = wave % WN, hh = lane >> 5, l32 = lane & 31;
+  // this lane's output row and its physical row
+  const int m = m0 + wm * 32 + l32, mc = min(m, M - 1);
+  int orow = mc;
+  if ((EPI == EPI_RESID || EPI == EPI_F32) && e.rows) orow = e.rows[mc];
+  f32x4_t bias[4];
+  const int nb = n0 + wn * 32;
+#pragma unroll
+  for (int q4 = 0; q4 < 4; q4++)
+    bias[q4] = *(const f32x4_t*)(e.bias + min(nb + 8 * q4 + 4 * hh, N - 4));
+  const bf16_t* sbase[DPW];
+  unsigned voff[DPW], dst[DPW];
+#pragma unroll
+  for (int u = 0; u < DPW; u++) {
+    const int q = wave * DPW + u;
+    const bool isA = q < MB / RPI;
+    const int r = (isA ? q : q - MB / RPI) * RPI + (lane >> 3);
+    const int gr = isA ? min(m0 + r, M - 1) : min(n0 + r, N - 1);
+    sbase[u] = isA ? A : W;
+    voff[u] = (unsigned)(((size_t)gr * (isA ? lda : K) + (((lane & 7) ^ (r & 7)) << 3)) * 2);
+    dst[u] = q * RPI * ROWB;
+  }
+  const int nk = K / KS;
+#pragma unroll
+  for (int st = 0; st < NSTG - 1; st++)
+    if (st < nk) {
+#pragma unroll
+      for (int u = 0; u < DPW; u++) dma16s(sbase[u] + st * KS, voff[u], lds0 + st * STGB + dst[u]);
+    }
+  f32x4_t xv[4];
+  float* xr = nullptr;
+  if (EPI == EPI_PATCH) {
+    const int s = mc / e.n0, j = mc - s * e.n0;
+    orow = s * (e.n0 + 1) + 1 + j;
+    xr = (float*)e.pos + (size_t)(1 + j) * e.ldo;
+  } else if (EPI == EPI_RESID) {
+    xr = (float*)e.out + (size_t)orow * e.ldo;
+  }
+  if (EPI == EPI_RESID || EPI == EPI_PATCH) {
+#pragma unroll
+    for (int q4 = 0; q4 < 4; q4++)
+      xv[q4] = *(const f32x4_t*)(xr + min(nb + 8 * q4 + 4 * hh, N - 4));
+  }
+  f32x16_t acc;
+#pragma unroll
+  for (int q4 = 0; q4 < 4; q4++)
+#pragma unroll
+    for (int q = 0; q < 4; q++) acc[4 * q4 + q] = bias[q4][q];
+  bf16x8_t fa[2][4], fb[2][4];
+  auto fetch = [&](int st, int p) {
+    const char* Ab = smem + st * STGB + (wm * 32 + l32) * ROWB;
+    const char* Bb = smem + st * STGB + (MB + wn * 32 + l32) * ROWB;
+#pragma unroll
+    for (int ks = 0; ks < 4; ks++) {
+      const int ch = ((2 * ks + hh) ^ (l32 & 7)) << 4;
+      fa[p][ks] = *(const bf16x8_t*)(Ab + ch);
+      fb[p][ks] = *(const bf16x8_t*)(Bb + ch);
+    }
+  };
+  // step kt: MFMAs on the operands in registers; operands of step kt + 1 read
+  // once its stage has landed; the stage of step kt + NSTG loaded into the
+  // slot that step kt was read from
+  auto landed = [&](int kt) {  // stage kt and every earlier one
+    if (kt + NSTG - 2 < nk)
+      wait_vm<DPW * (NSTG - 2)>();
+    else
+      wait_vm<0>();
+    if (NWV > 1) __syncthreads();
+  };
+  int sr = 0, sw = NSTG - 1;
+  auto step = [&](int kt, int p) {
+    if (kt + 1 < nk) {
+      if (kt + NSTG - 1 < nk) {
+        // (slot sw held step kt - 1, whose operands every wave has read)
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int u = 0; u < DPW; u++)
+          dma16s(sbase[u] + (kt + NSTG - 1) * KS, voff[u], lds0 + sw * STGB + dst[u]);
+        sw = sw + 1 == NSTG ? 0 : sw + 1;
+      }
+      sr = sr + 1 == NSTG ? 0 : sr + 1;
+      landed(kt + 1);
+      if (mm) fetch(sr, p ^ 1);
+    }
+    if (mm)
+#pragma unroll
+    for (int ks = 0; ks < 4; ks++)
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[p][ks], fa[p][ks], acc, 0, 0, 0);
+  };
+  landed(0);
+  if (mm) fetch(0, 0);
+  for (int kt = 0; kt < nk; kt += 2) {
+    step(kt, 0);
+    if (kt + 1 < nk) step(kt + 1, 1);
+  }
+  if (m >= M || !mm) return;
+#pragma unroll
+  for (int q4 = 0; q4 < 4; q4++) {
+    const int n = nb + 8 * q4 + 4 * hh;
+    if (n >= N) continue;
+    f32x4_t v = {acc[4 * q4], acc[4 * q4 + 1], acc[4 * q4 + 2], acc[4 * q4 + 3]};
+    if (EPI == EPI_STORE || EPI == EPI_GELU) {
+      if (EPI == EPI_GELU) {
+#pragma unroll
+        for (int q = 0; q < 4; q++) v[q] = gelu_erf(v[q]);
+      }
+      *(uint2*)((bf16_t*)e.out + (size_t)m * e.ldo + n) =
+          make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+    } else {
+      if (EPI == EPI_RESID) v = xv[q4] + v;
+      if (EPI == EPI_PATCH) v = v + xv[q4];
+      *(f32x4_t*)((float*)e.out + (size_t)orow * e.ldo + n) = v;
+    }
+  }
+}
+
+// Workgroups by the number of 32 x 32 blocks (us per launch at the rows, N x
+// K given; large-tile kernel / 1 block / 2 blocks / 4 blocks a workgroup):
+//   up to 256, one per CU: one block and four loading waves
+//     (197, 384 x 1536: 15.2 / 6.9 / 8.2 / 9.5; 197, 1152 x 384: 5.3 / 3.5 / 3.8 / 4.6)
+//   up to 900: two blocks (788, 1152 x 384: 5.6 / 5.0 / 4.7 / 5.1)
+//   up to SMALL_TILES: four blocks, which load each operand row for two
+//     (1576, 1152 x 384: 6.9 / 8.2 / 7.7 / 6.2; 2400, 768 x 3072: 35.6 / 41 / 37 / 26)
+//   beyond, the 64- and 128-row tiles (2400, 1152 x 384: 7.9 against 8.1)
+template <int EPI>
+void launch_small(const bf16_t* A, int lda, const bf16_t* W, int N, int K, const int* M_dev,
+                  int M_host, int M_ub, long t32, const Epi& e, hipStream_t s) {
+  const int m32 = (M_ub + 31) / 32, m64 = (M_ub + 63) / 64, n64 = (N + 63) / 64;
+  if (t32 <= 256)
+    gemm_mfma_bf16_small<EPI, 1, 1, 4, 4><<<(int)t32, 256, 0, s>>>(A, lda, W, N, K, M_dev, M_host, e);
+  else if (t32 <= 900)
+    gemm_mfma_bf16_small<EPI, 1, 2, 4, 4><<<m32 * n64, 256, 0, s>>>(A, lda, W, N, K, M_dev, M_host, e);
+  else
+    gemm_mfma_bf16_small<EPI, 2, 2, 3, 4><<<m64 * n64, 256, 0, s>>>(A, lda, W, N, K, M_dev, M_host, e);
+}
+
 // ------------------------------------------------------------ fp32 MFMA --
 // MB x MB output tile per workgroup, 4 waves in a 2 x 2 grid, each wave
 // (MB / 32)^2 blocks of v_mfma_f32_16x16x4_f32.  K is consumed 16 floats at a
@@ -686,6 +857,18 @@ hipError_t launch_gemm<bf16_t>(const bf16_t* A, int lda, const bf16_t* W,
     return hipErrorInvalidValue;
   if ((e.mode == EPI_STORE || e.mode == EPI_GELU) && (N % 8 != 0 || e.ldo % 8 != 0))
     return hipErrorInvalidValue;
+  const long t32 = (long)((M_ub + 31) / 32) * ((N + 31) / 32);
+  if (K % 64 == 0 && t32 <= SMALL_TILES) {
+    switch (e.mode) {
+      case EPI_STORE: launch_small<EPI_STORE>(A, lda, W, N, K, M_dev, M_host, M_ub, t32, e, s); break;
+      case EPI_GELU: launch_small<EPI_GELU>(A, lda, W, N, K, M_dev, M_host, M_ub, t32, e, s); break;
+      case EPI_RESID: launch_small<EPI_RESID>(A, lda, W, N, K, M_dev, M_host, M_ub, t32, e, s); break;
+      case EPI_F32: launch_small<EPI_F32>(A, lda, W, N, K, M_dev, M_host, M_ub, t32, e, s); break;
+      case EPI_PATCH: launch_small<EPI_PATCH>(A, lda, W, N, K, M_dev, M_host, M_ub, t32, e, s); break;
+      default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
   const int n_nt = (N + NB - 1) / NB;
   // tile rows: 256 (8 waves) when there are enough tiles to fill the CUs
   // several times over, 64 when 128-row tiles would leave CUs idle

@@ -92,6 +92,49 @@ def test_gemm_bf16(torch_cuda, M, N, K, epi):
     assert np.array_equal(g[untouched], x0[untouched])
 
 
+@pytest.mark.parametrize("M,N,K,epi", [
+    (1, 64, 64, "store"), (33, 72, 192, "gelu"), (31, 36, 320, "resid"), (257, 1000, 64, "f32"),
+    (197, 384, 1536, "resid"),                                  # one block per workgroup
+    (300, 1152, 384, "store"), (511, 1004, 128, "resid"),       # two blocks
+    (1000, 1536, 384, "gelu"), (2047, 384, 448, "resid"), (2017, 1000, 64, "f32"),  # four blocks
+])
+def test_gemm_bf16_small_launches(torch_cuda, M, N, K, epi):
+    """Launches with few tiles: against float64, and (N % 8 == 0) bit for bit
+    the rows that a launch with thousands of tiles gives."""
+    torch = torch_cuda
+    print(f"[gemm bf16 small] M={M} N={N} K={K} epi={epi}", flush=True)
+    rng = np.random.default_rng(M + N + K)
+    A, W = _bf16(rng, (M, K)), _bf16(rng, (N, K), 0.05)
+    bias = rng.standard_normal(N).astype(np.float32) * 0.1
+    dA, dW = _to_dev_bf16(torch, A), _to_dev_bf16(torch, W)
+    db = torch.from_numpy(bias).cuda()
+    x0 = rng.standard_normal((M, N)).astype(np.float32)
+    fp32 = epi in ("resid", "f32")
+
+    def run(times):
+        rows = torch.randperm(M * times, device="cuda").int() if fp32 else None
+        out = torch.from_numpy(x0).cuda().to(torch.float32 if fp32 else torch.bfloat16)
+        out = out.repeat(times, 1)
+        if fp32:
+            out[rows.long()] = out.clone()  # the row of A's row r is rows[r]
+        _kern().gemm(dA.repeat(times, 1), dW, db, epi, out, rows)
+        return (out[rows.long()] if fp32 else out).float().cpu().numpy()
+
+    g = run(1)
+    ref = A.astype(np.float64) @ W.astype(np.float64).T + bias
+    bound = np.abs(A).astype(np.float64) @ np.abs(W).astype(np.float64).T
+    if fp32:
+        want = ref + (x0 if epi == "resid" else 0.0)
+        tol = 1e-5 * (bound + np.abs(x0)) + 1e-6
+    else:
+        want = fo.gelu(ref.astype(np.float32)) if epi == "gelu" else ref
+        tol = 2.0 ** -8 * np.abs(want) + 1e-5 * bound + 1e-6
+    assert (np.abs(g - want) <= tol).all()
+    if N % 8 == 0:
+        times = 2400 * 32 * 32 // (M * N) + 1  # beyond the small launches
+        assert np.array_equal(run(times).reshape(times, M, N), np.broadcast_to(g, (times, M, N)))
+
+
 @pytest.mark.parametrize("M,N,K", [(6000, 1536, 384), (20000, 1536, 384), (12000, 768, 192),
                                    (6000, 3072, 768)])
 def test_gemm_gelu_fc1_shapes(torch_cuda, M, N, K):
