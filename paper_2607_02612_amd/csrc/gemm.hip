@@ -210,25 +210,32 @@ __global__ __launch_bounds__(MB / (32 * WR) * 128, MB == 128 ? 3 : 1) void gemm_
   // the accumulators start at the bias of their columns (lane l owns columns
   // n0 + wn 64 + 32 j + 8 (q / 4) + 4 (l / 32) + q % 4; columns past N, never
   // stored, take a clamped bias), so no epilogue adds it
-  // (the column base is clamped as a whole: with N % 8 == 0 the lane
-  // halves' columns c and c + 4 stay inside the bias vector; each
-  // accumulator set loads its own copy, which costs no vector ALU moves)
+  // (with N % 8 == 0 the column base is clamped as a whole, since the lane
+  // halves' columns c and c + 4 are on the same side of N: the addresses are
+  // scalar; else each lane clamps its own.  Each accumulator set loads its
+  // own copy, which costs no vector ALU moves)
   f32x16_t acc[WR][2];
-  const float* bias_l = e.bias + 4 * (lane >> 5);
+  auto load_bias = [&](auto col) {
 #pragma unroll
-  for (int j = 0; j < 2; j++)
+    for (int j = 0; j < 2; j++)
 #pragma unroll
-    for (int q4 = 0; q4 < 4; q4++) {
-      const int cb = min(n0 + wn * 64 + j * 32 + 8 * q4, N - 8);
+      for (int q4 = 0; q4 < 4; q4++) {
+        const float* bp = col(n0 + wn * 64 + j * 32 + 8 * q4);
 #pragma unroll
-      for (int i = 0; i < WR; i++) {
-        const float4 bv = *(const float4*)(bias_l + cb);
-        acc[i][j][4 * q4 + 0] = bv.x;
-        acc[i][j][4 * q4 + 1] = bv.y;
-        acc[i][j][4 * q4 + 2] = bv.z;
-        acc[i][j][4 * q4 + 3] = bv.w;
+        for (int i = 0; i < WR; i++) {
+          const float4 bv = *(const float4*)bp;
+          acc[i][j][4 * q4 + 0] = bv.x;
+          acc[i][j][4 * q4 + 1] = bv.y;
+          acc[i][j][4 * q4 + 2] = bv.z;
+          acc[i][j][4 * q4 + 3] = bv.w;
+        }
       }
-    }
+  };
+  const float* bias_l = e.bias + 4 * (lane >> 5);
+  if (EPI == EPI_STORE || EPI == EPI_GELU || N % 8 == 0)
+    load_bias([&](int c) { return bias_l + min(c, N - 8); });
+  else
+    load_bias([&](int c) { return e.bias + min(c + 4 * (lane >> 5), N - 4); });
 
   // this lane's source row and LDS slot for each of the wave's DMA
   // instructions (8-row blocks: A rows first, then W rows)
