@@ -13,6 +13,8 @@
 // on scheduling or on the rest of the batch.
 #include "kernels.h"
 
+#include <algorithm>
+
 namespace fusion {
 
 constexpr int AD_TMAX = 640;  // tokens per sample (CLS included), largest size class
@@ -811,27 +813,34 @@ hipError_t launch_adapt(const AdaptArgs& a, hipStream_t s) {
 // --------------------------------------------------------- compaction --
 // Grid: (live sample, part); every workgroup of a sample recomputes the
 // sample's offsets (cheap scans) and moves one contiguous range of its rows.
-constexpr int CP_PARTS = 8;
-template <typename T>
+// Bound by a chain of dependent loads (counters, lengths, keep flags, row id,
+// row) when the batch is small, else by the rows read and their LayerNorm
+// written.  Each wave takes all keep flags of the sample in one batch of
+// loads and counts a token's packed slot in their ballots, and a small batch
+// is split into more parts: 13.9 -> 12.9 us per launch for DeiT-S at batch
+// 256, 7.7 -> 5.3 us at batch 1, 14.8 -> 11.0 us for 64 samples at 384 x 384.
+// CP_CHUNKS: wave masks that cover the longest sample.
+template <typename T, int CP_CHUNKS>
 __global__ __launch_bounds__(256) void compact_kernel(CompactArgs a) {
   const int i = blockIdx.x, part = blockIdx.y;
   const int nl = a.cnt->nlive;
   // Workgroup (0, 0) always publishes the next counters, also when no sample
   // is live any more (the next block must see nlive = 0, not a stale value).
   if (i >= nl && (i != 0 || part != 0)) return;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, lane = tid & 63;
   __shared__ int ired[8];
-  __shared__ int dsts[AD_TMAX];
-  __shared__ int chunk_off[AD_TMAX / 64 + 1];
+  __shared__ int dsts[AD_TMAX / 8], prow[AD_TMAX / 8];  // packed slot (-1: dropped), physical row
 
   int off = 0, j = 0;
-  for (int t = tid; t < i; t += 256) {
-    const int n = a.newlen[t];
-    off += n;
-    j += n > 0;
+  if (i > 0) {
+    for (int t = tid; t < i; t += 256) {
+      const int n = a.newlen[t];
+      off += n;
+      j += n > 0;
+    }
+    off = block_sum256_i(off, ired);
+    j = block_sum256_i(j, ired);
   }
-  off = block_sum256_i(off, ired);
-  j = block_sum256_i(j, ired);
   if (i == 0 && part == 0) {
     int tot = 0, nn = 0;
     for (int t = tid; t < nl; t += 256) {
@@ -849,59 +858,55 @@ __global__ __launch_bounds__(256) void compact_kernel(CompactArgs a) {
   }
   if (i >= nl || a.newlen[i] == 0) return;
   const int base = a.cu[i], Tn = a.cu[i + 1] - base;
-  if (Tn > AD_TMAX) return;  // never kept by the adapt kernel (newlen 0)
+  if (Tn > 64 * CP_CHUNKS || Tn > a.n0 + 1 || Tn < 1) return;  // never kept by the adapt kernel (newlen 0)
   const int orig = a.live[i];
   if (tid == 0 && part == 0) {
     a.cu2[j] = off;
     a.live2[j] = orig;
   }
-  const int nch = (Tn + 63) / 64;
-  for (int c = wave; c < nch; c += 4) {
-    const int t = c * 64 + lane;
-    const unsigned long long msk = __ballot(t < Tn && a.keep[base + t]);
-    if (lane == 0) chunk_off[c] = __popcll(msk);
-  }
-  __syncthreads();
-  if (tid == 0) {
-    int run = 0;
-    for (int c = 0; c < nch; c++) {
-      const int n = chunk_off[c];
-      chunk_off[c] = run;
-      run += n;
-    }
-  }
-  __syncthreads();
-  for (int c = wave; c < nch; c += 4) {
-    const int t = c * 64 + lane;
-    const bool f = t < Tn && a.keep[base + t];
-    const unsigned long long msk = __ballot(f);
-    const int pos = __popcll(msk & ((1ull << lane) - 1ull));
-    if (t < Tn) dsts[t] = f ? chunk_off[c] + pos : -1;
-  }
-  __syncthreads();
-  // kept rows of this part (the sample's rows split into CP_PARTS ranges):
-  // when asked, one half wave per row writes its LayerNorm for the next
-  // block (16-byte pieces); the row itself stays where it is, only its
-  // physical row id, size and origin move to the packed slot
-  const int per = (Tn + CP_PARTS - 1) / CP_PARTS;
+  // this part's rows (the sample's rows split into gridDim.y ranges)
+  const int per = (Tn + (int)gridDim.y - 1) / (int)gridDim.y;
   const int t0 = part * per, t1 = min(Tn, t0 + per);
-  if (a.ln_out) {
-    for (int t = t0 + (tid >> 5); t < t1; t += 8) {
-      const int dj = dsts[t];
-      if (dj < 0) continue;
-      const size_t dr = (size_t)(off + dj);
-      ln_row_half<T>(a.x + (size_t)a.rmap[base + t] * a.d, a.d, lane & 31, a.ln_g, a.ln_b,
-                     (T*)a.ln_out + dr * a.d, nullptr);
+  if (t0 >= t1) return;
+  // one thread per row of the part (AD_TMAX rows in at least 8 parts): its row id, size and origin move to the packed slot
+  const bool mine = tid < t1 - t0;
+  const int t = t0 + tid, tb = base + (mine ? t : t0);
+  const int pr = a.rmap[tb], og = a.origin[tb];
+  const float sz = a.size[tb];
+  int kf[CP_CHUNKS];
+#pragma unroll
+  for (int c = 0; c < CP_CHUNKS; c++)
+    if (c * 64 < t1) kf[c] = a.keep[base + min(c * 64 + lane, Tn - 1)];
+  int n = 0;
+  unsigned long long m = 0;
+#pragma unroll
+  for (int c = 0; c < CP_CHUNKS; c++)
+    if (c * 64 < t1) {
+      const unsigned long long msk = __ballot(c * 64 + lane < Tn && kf[c] != 0);
+      n += c < (t >> 6) ? __popcll(msk) : 0;
+      m = c == (t >> 6) ? msk : m;
+    }
+  const unsigned long long bit = 1ull << (t & 63);
+  if (mine) {
+    const int dj = (m & bit) ? n + __popcll(m & (bit - 1ull)) : -1;
+    dsts[tid] = dj;
+    prow[tid] = pr;
+    if (dj >= 0) {
+      a.rmap2[off + dj] = pr;
+      a.size2[off + dj] = sz;
+      a.origin2[off + dj] = og;
+      if (a.tr_ids) a.tr_ids[((size_t)(a.b - 1) * a.B + orig) * (a.n0 + 1) + dj] = og;
     }
   }
-  for (int t = t0 + tid; t < t1; t += 256) {
-    const int dj = dsts[t];
+  if (!a.ln_out) return;
+  __syncthreads();
+  // one half wave per kept row writes its LayerNorm for the next block
+  // (16-byte pieces); the row itself stays where it is
+  for (int q = tid >> 5; q < t1 - t0; q += 8) {
+    const int dj = dsts[q];
     if (dj < 0) continue;
-    a.rmap2[off + dj] = a.rmap[base + t];
-    a.size2[off + dj] = a.size[base + t];
-    a.origin2[off + dj] = a.origin[base + t];
-    if (a.tr_ids)
-      a.tr_ids[((size_t)(a.b - 1) * a.B + orig) * (a.n0 + 1) + dj] = a.origin[base + t];
+    ln_row_half<T>(a.x + (size_t)prow[q] * a.d, a.d, lane & 31, a.ln_g, a.ln_b,
+                   (T*)a.ln_out + (size_t)(off + dj) * a.d, nullptr);
   }
 }
 
@@ -909,7 +914,15 @@ template <typename T>
 hipError_t launch_compact(const CompactArgs& a, hipStream_t s) {
   if (a.nlive_ub <= 0) return hipSuccess;
   if (a.n0 + 1 > AD_TMAX || a.d % 4 != 0 || a.d > 4 * 32 * LN_MAXV) return hipErrorInvalidValue;
-  compact_kernel<T><<<dim3(a.nlive_ub, CP_PARTS), 256, 0, s>>>(a);
+  // 8 parts per sample, more while the launch stays under 1024 workgroups, up
+  // to one row per half wave (per launch, averaged over the blocks of a run,
+  // with 8 / more parts: 1 sample of 197 tokens 6.5 / 5.3 us, 64 samples of
+  // 577 12.8 / 11.0; 4096 workgroups were slower at 256 samples, 17.0 / 12.9)
+  const int parts = std::min((a.n0 + 1 + 7) / 8, std::max(8, 1024 / a.nlive_ub));
+  if (a.n0 + 1 <= 256)
+    compact_kernel<T, 4><<<dim3(a.nlive_ub, parts), 256, 0, s>>>(a);
+  else
+    compact_kernel<T, AD_TMAX / 64><<<dim3(a.nlive_ub, parts), 256, 0, s>>>(a);
   return hipGetLastError();
 }
 template hipError_t launch_compact<float>(const CompactArgs&, hipStream_t);
