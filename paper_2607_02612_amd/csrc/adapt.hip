@@ -11,6 +11,17 @@
 // One 512-thread workgroup per live sample (the compaction uses 256).  No
 // float atomics: every reduction has a fixed order, so results do not depend
 // on scheduling or on the rest of the batch.
+//
+// The per-sample kernel is a chain of short dependent phases, bound by their
+// latency (one workgroup per CU, few waves): it loads what a phase needs
+// together with the phase before, reduces with lane moves instead of LDS
+// shuffles, ranks four keys per LDS read or searches thresholds within a wave,
+// and keeps two barriers between the choice of the pairs and the merge.
+// Per launch, averaged over the blocks of a run: one 224 x 224 image 21.3 ->
+// 17.7 us (blocks of 130 to 197 tokens) and 14.1 -> 12.7 us (up to 128), 64
+// images with few merges 17.9 -> 12.9 us, 64 images at 384 x 384 21.8 -> 13.9
+// us and 26.0 -> 23.2 us for similarity_kernel.  Of 37,000 cycles at 189
+// tokens the similarity takes 26,500.
 #include "kernels.h"
 
 #include <algorithm>
@@ -64,10 +75,11 @@ __device__ __forceinline__ int merge_count(float m, double rho, int r_b, int N, 
   return r;
 }
 
-// Block-wide reductions for AD_NT threads (8 waves); red >= 8 entries.
+// Block-wide reductions for AD_NT threads (8 waves).  red: 8 entries that no
+// thread still reads; every write of the workgroup before the call is visible
+// after it.
 __device__ __forceinline__ float bsum(float v, float* red) {
   v = wave_sum(v);
-  __syncthreads();
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   float s = 0.f;
@@ -77,43 +89,12 @@ __device__ __forceinline__ float bsum(float v, float* red) {
 }
 __device__ __forceinline__ float bmax(float v, float* red) {
   v = wave_max(v);
-  __syncthreads();
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   float s = red[0];
 #pragma unroll
   for (int w = 1; w < AD_NT / 64; w++) s = fmaxf(s, red[w]);
   return s;
-}
-__device__ __forceinline__ int bsum_i(int v, int* red) {
-  v = wave_sum_i(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  int s = 0;
-#pragma unroll
-  for (int w = 0; w < AD_NT / 64; w++) s += red[w];
-  return s;
-}
-
-// Stream compaction over the workgroup (one candidate per thread): writes
-// the indices `v` of the threads with `f` set to out[0 ..) in thread order
-// and returns their count.  red >= AD_NT / 64 ints.
-__device__ __forceinline__ int block_compact(bool f, int v, int* out, int* red) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const unsigned long long msk = __ballot(f);
-  __syncthreads();
-  if (lane == 0) red[wave] = __popcll(msk);
-  __syncthreads();
-  int off = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < AD_NT / 64; w++) {
-    off += w < wave ? red[w] : 0;
-    tot += red[w];
-  }
-  if (f) out[off + __popcll(msk & ((1ull << lane) - 1ull))] = v;
-  __syncthreads();
-  return tot;
 }
 
 // Lanes that share one element's rank count when n elements are ranked by
@@ -123,100 +104,101 @@ __device__ __forceinline__ int rank_lanes(int n) {
   while (P < 16 && n * (2 * P) <= AD_NT) P *= 2;
   return P;
 }
+// Sum over the P adjacent lanes (P = 1, 2, 4, 8 or 16) of each group.
+__device__ __forceinline__ int lanes_sum(int v, int P) {
+  if (P > 1) v += lane_xor_i<1>(v);
+  if (P > 2) v += lane_xor_i<2>(v);
+  if (P > 4) v += lane_xor_i<4>(v);
+  if (P > 8) v += lane_xor_i<8>(v);
+  return v;
+}
 
-// Order-preserving key of a float: for a, b not NaN, a < b iff
+// Order-preserving key of a float, never 0: for a, b not NaN, a < b iff
 // order_key(a) < order_key(b), and a == b iff the keys are equal (-0 and +0
-// share the key of +0).
+// share the key of +0).  NaNs take keys of their own at the two ends.
 __device__ __forceinline__ unsigned order_key(float f) {
   const unsigned u = f == 0.f ? 0u : __float_as_uint(f);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  const unsigned k = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  return k ? k : 1u;
 }
 
-// Top-c selection over the workgroup, E (1 or 2) elements per thread:
-// e = tid (key k0, taking part if ok0) and e = tid + AD_NT (k1, ok1).  An
-// element is chosen iff it takes part and fewer than c participating
-// elements precede it, a larger key or an equal key at a lower e coming
-// first: the rank rule of the merge and prune selections (ties to the lower
-// slot), without the all-pairs comparisons.  The c-th largest key is found
-// two bits at a time from the top: per round one workgroup count of the
-// candidates whose next two bits are >= 1, >= 2 and 3 (a ballot per wave
-// and count, the wave counts in LDS slots used alternately, so one barrier
-// per round); then the elements equal to it are taken in ascending e until
-// c are chosen.  cnt: 6 * AD_NT / 64 ints of LDS; the caller synchronises
-// before reusing them.
-template <int E>
-__device__ __forceinline__ void block_top(unsigned k0, bool ok0, unsigned k1, bool ok1, int c,
-                                          bool& ch0, bool& ch1, int* cnt) {
-  constexpr int NW = AD_NT / 64;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  if (E < 2) ok1 = false;
-  ch0 = ch1 = false;
+// Selections rank keys[0 .. n), padded with 0 up to a multiple of 4 (rank_of)
+// or 64 (wave_top); key 0 marks an element that does not take part.  An
+// element is chosen iff fewer than c elements precede it, a larger key or an
+// equal key at a lower index coming first.
+//
+// rank_of: elements that precede e (key k >= 1), counted over this lane's
+// share (lane p of P) of the keys, four to a 16-byte LDS read: at indices
+// below e a key of at least k counts, above it one larger than k, which is
+// one compare and one add with carry per key outside e's own group of four.
+__device__ __forceinline__ int rank_of(const unsigned* keys, int n, int e, unsigned k, int p,
+                                       int P) {
+  int rank = 0;
+  const int n4 = (n + 3) >> 2, qe = e >> 2;
+#pragma unroll 4
+  for (int q = p; q < n4; q += P) {
+    const uint4 v = ((const uint4*)keys)[q];
+    const unsigned t = q < qe ? k - 1u : k;
+    rank += v.x > t;
+    rank += v.y > t;
+    rank += v.z > t;
+    rank += v.w > t;
+  }
+  if (qe % P == p) {  // equal keys below e in its own group
+    const uint4 v = ((const uint4*)keys)[qe];
+    rank += ((e & 3) > 0) & (v.x == k);
+    rank += ((e & 3) > 1) & (v.y == k);
+    rank += ((e & 3) > 2) & (v.z == k);
+  }
+  return rank;
+}
+
+// wave_top: the c elements chosen of n <= 64 NJ, as this wave's ballots; bit
+// l of sel[j] is element 64 j + l.  The c-th largest key is found bit by bit
+// from the top: the wave holds all keys in registers and counts those at or
+// above the next threshold with ballots, so there is no LDS round trip and no
+// barrier in the search (a workgroup-wide digit search with one barrier per
+// round took 7,000 to 13,000 cycles for 288 keys), which ends early once
+// exactly c keys remain.
+template <int NJ>
+__device__ __forceinline__ void wave_top(const unsigned* keys, int n, int c,
+                                         unsigned long long (&sel)[NJ]) {
+  const int lane = threadIdx.x & 63;
+  const int nj = (n + 63) >> 6;
+  c = __builtin_amdgcn_readfirstlane(c);
+  unsigned k[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; j++) {
+    k[j] = j < nj ? keys[64 * j + lane] : 0u;
+    sel[j] = 0ull;
+  }
   if (c <= 0) return;
-  unsigned prefix = 0, mask = 0;
-  int need = c, slot = 1;
-  for (int bit = 30; bit >= 0; bit -= 2) {
-    const bool m0 = ok0 && (k0 & mask) == prefix, m1 = ok1 && (k1 & mask) == prefix;
-    const unsigned g0 = (k0 >> bit) & 3u, g1 = (k1 >> bit) & 3u;
-    int n[3];
+  unsigned prefix = 0;
+  for (int bit = 31; bit >= 0; bit--) {
+    const unsigned t = prefix | (1u << bit);
+    int m = 0;
 #pragma unroll
-    for (int q = 0; q < 3; q++) {
-      n[q] = __popcll(__ballot(m0 && g0 >= (unsigned)(q + 1)));
-      if (E > 1) n[q] += __popcll(__ballot(m1 && g1 >= (unsigned)(q + 1)));
-    }
-    if (lane == 0) {
-#pragma unroll
-      for (int q = 0; q < 3; q++) cnt[(slot * 3 + q) * NW + wave] = n[q];
-    }
-    __syncthreads();
-    int ge[3] = {0, 0, 0};  // candidates whose next two bits are >= 1, >= 2, == 3
-#pragma unroll
-    for (int q = 0; q < 3; q++)
-#pragma unroll
-      for (int w = 0; w < NW; w++) ge[q] += cnt[(slot * 3 + q) * NW + w];
-    slot ^= 1;
-    unsigned g;
-    if (ge[2] >= need) {
-      g = 3u;
-    } else if (ge[1] >= need) {
-      g = 2u;
-      need -= ge[2];
-    } else if (ge[0] >= need) {
-      g = 1u;
-      need -= ge[1];
-    } else {
-      g = 0u;
-      need -= ge[0];
-    }
-    prefix |= g << bit;
-    mask |= 3u << bit;
+    for (int j = 0; j < NJ; j++) m += (int)__popcll(__ballot(k[j] >= t));
+    if (m >= c) prefix = t;
+    if (m == c) break;  // the keys from the threshold on are the c largest
   }
-  // the elements equal to the c-th key, in ascending e: all of the first
-  // half (e < AD_NT) come before the second
-  const bool eq0 = ok0 && k0 == prefix, eq1 = ok1 && k1 == prefix;
-  const unsigned long long b0 = __ballot(eq0), b1 = E > 1 ? __ballot(eq1) : 0ull;
-  __syncthreads();
-  if (lane == 0) {
-    cnt[wave] = __popcll(b0);
-    cnt[NW + wave] = __popcll(b1);
-  }
-  __syncthreads();
-  int before0 = 0, before1 = 0, tot0 = 0;
+  // prefix is at most the c-th key and above the next one: all larger keys,
+  // then equal ones in index order
+  int need = c;
 #pragma unroll
-  for (int w = 0; w < NW; w++) {
-    tot0 += cnt[w];
-    before0 += w < wave ? cnt[w] : 0;
-    before1 += w < wave ? cnt[NW + w] : 0;
-  }
+  for (int j = 0; j < NJ; j++) need -= (int)__popcll(__ballot(k[j] > prefix));
   const unsigned long long lt = (1ull << lane) - 1ull;
-  const int r0 = before0 + __popcll(b0 & lt);
-  const int r1 = tot0 + before1 + __popcll(b1 & lt);
-  ch0 = ok0 && (k0 > prefix || (eq0 && r0 < need));
-  ch1 = ok1 && (k1 > prefix || (eq1 && r1 < need));
+#pragma unroll
+  for (int j = 0; j < NJ; j++) {
+    const unsigned long long eq = __ballot(k[j] == prefix);
+    sel[j] = __ballot(k[j] > prefix || (k[j] == prefix && (int)__popcll(eq & lt) < need));
+    need = max(need - (int)__popcll(eq), 0);
+  }
 }
 
-// Candidates above which block_top replaces the all-pairs rank count (its
-// rounds cost about as much as 256 rank comparisons per thread).
-constexpr int SEL_RADIX_MIN = 256;
+// Candidates above which wave_top replaces the all-pairs rank count (whole
+// prune step at 188 candidates: 4,800 against 8,300 cycles).
+constexpr int SEL_WAVE_MIN = 128;
 
 // Cosine similarities of the A tokens (even patch slots) with the B tokens
 // (odd slots) of one sample, and the best B for every A.
@@ -258,6 +240,7 @@ __device__ void similarity_argmax(const float* __restrict__ x, const int* prow, 
   constexpr int Q = SKC / 4;  // 16-byte slots per row and chunk
   static_assert(SKC % 32 == 0, "whole MFMA K steps per chunk");
   static_assert(SPT * AD_NT == (SAG + BMAX) * Q, "slots must tile the staged rows exactly");
+  static_assert(Q == 8 || Q == 16, "lanes of a staged row");
   static_assert(NBW % BG == 0 && NBW * WC == Z::NBT, "wave layout: B tiles split evenly");
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int g = lane >> 4, c = lane & 15;
@@ -358,12 +341,20 @@ __device__ void similarity_argmax(const float* __restrict__ x, const int* prow, 
       }
     };
     // chunk kc: MFMAs on buffer kc & 1; chunk kc + 1 (in registers `nx`)
-    // staged into the other buffer; chunk kc + 3 loaded into `nx`
+    // staged into the other buffer; chunk kc + 3 loaded into `nx`.  The two
+    // do not depend on each other: of the two waves on each SIMD one stages
+    // first, so that vector and matrix work overlap.
     float4 r0[SPT], r1[SPT];
     auto step = [&](int kc, float4(&nx)[SPT]) {
-      mfma(kc & 1);
-      if (kc + 1 < nck) stage(nx, (kc + 1) & 1);
-      if (kc + 3 < nck) load(nx, kc + 3);
+      if (wave & 4) {
+        if (kc + 1 < nck) stage(nx, (kc + 1) & 1);
+        if (kc + 3 < nck) load(nx, kc + 3);
+        mfma(kc & 1);
+      } else {
+        mfma(kc & 1);
+        if (kc + 1 < nck) stage(nx, (kc + 1) & 1);
+        if (kc + 3 < nck) load(nx, kc + 3);
+      }
       __syncthreads();
     };
     load(r0, 0);
@@ -379,14 +370,18 @@ __device__ void similarity_argmax(const float* __restrict__ x, const int* prow, 
 #pragma unroll
     for (int w = 0; w < SPT; w++) {
       float v = ss[w];
-#pragma unroll
-      for (int o = 1; o < Q; o <<= 1) v += __shfl_xor(v, o, 64);
+      v += lane_xor<1>(v);
+      v += lane_xor<2>(v);
+      v += lane_xor<4>(v);
+      if (Q > 8) v += lane_xor<8>(v);
       const int u = tid + w * AD_NT;
-      if (sval[w] && (u % Q) == 0) rn[u / Q] = 1.0f / fmaxf(sqrtf(v), 1e-12f);
+      // (the B rows of the padding get a NaN, whose products never win)
+      if ((u % Q) == 0 && (sval[w] || u / Q >= SAG))
+        rn[u / Q] = sval[w] ? 1.0f / fmaxf(sqrtf(v), 1e-12f) : NAN;
     }
     __syncthreads();
-    // best B per A over this wave's tiles; rows and columns past nA / nB
-    // read clamped or stale norms and are masked
+    // best B per A over this wave's tiles (A rows past nA are never read; a
+    // wave without a real pair has zero products, kept out by `act`)
 #pragma unroll
     for (int i = 0; i < 2; i++) {
       const int ar = 32 * wr + 16 * i + c;  // A row within the pass
@@ -401,7 +396,7 @@ __device__ void similarity_argmax(const float* __restrict__ x, const int* prow, 
 #pragma unroll
         for (int j = 0; j < 4; j++) {
           const float v = (acc[i][t][j] * ra) * rbj[j];
-          const bool take = act && b0 + j < nB && v > bv;
+          const bool take = v > bv;
           bv = take ? v : bv;
           bi = take ? b0 + j : bi;
         }
@@ -427,8 +422,8 @@ __device__ void similarity_argmax(const float* __restrict__ x, const int* prow, 
         bi = t1 ? i1 : i0;
       }
       if (g == 0) {
-        pbv[wc * SAG + ar] = bv;
-        pbi[wc * SAG + ar] = bi;
+        pbv[wc * SAG + ar] = act ? bv : -INFINITY;
+        pbi[wc * SAG + ar] = act ? bi : 0x7fffffff;
       }
     }
     __syncthreads();
@@ -452,18 +447,22 @@ __device__ void similarity_argmax(const float* __restrict__ x, const int* prow, 
   }
 }
 
-template <class Z>
+// Samples whose merge step has its best matches from similarity_kernel keep no
+// similarity operands in LDS (SIM = false).
+template <class Z, bool SIM>
 __global__ __launch_bounds__(AD_NT) void adapt_kernel(AdaptArgs a) {
   const int i = blockIdx.x;
-  if (i >= a.cnt->nlive) return;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  // (the offsets and the live map hold an entry per workgroup of the grid:
+  // nothing here waits for the counter)
   const int base = a.cu[i], T = a.cu[i + 1] - base, N = T - 1;
   const int orig = a.live[i];
+  if (i >= a.cnt->nlive) return;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int d = a.d;
   const size_t tr_row = (size_t)(a.b - 1) * a.B + orig;
 
   constexpr int TMAX = Z::TMAX, AMAX = Z::AMAX, BMAX = Z::BMAX, SKP = Z::SKP, SAG = Z::SAG;
-  static_assert(AMAX <= AD_NT && TMAX - 1 <= 2 * AD_NT, "block_top covers every candidate");
+  static_assert(AMAX <= AD_NT && TMAX % 64 == 0 && AMAX % 64 == 0, "selection ranges");
   // the host's token bound selects the size class and is exact; a sample
   // beyond it (never produced by the library itself) is dropped rather than
   // overrunning the per-token LDS arrays
@@ -475,31 +474,31 @@ __global__ __launch_bounds__(AD_NT) void adapt_kernel(AdaptArgs a) {
   __shared__ float szs[TMAX];
   __shared__ int prow[TMAX];  // physical row of x for each of the sample's tokens
   __shared__ int keepf[TMAX];
-  __shared__ int knew[TMAX];
-  __shared__ __attribute__((aligned(16))) float rn[TMAX];  // reciprocal norms
+  // reciprocal norms of the similarity, then the keys of the selections
+  __shared__ __attribute__((aligned(16))) float rn[TMAX];
+  unsigned* keys = (unsigned*)rn;
   __shared__ float bestsim[AMAX];
   __shared__ int best[AMAX];
-  __shared__ int chosen[AMAX];
-  __shared__ int clist[AMAX];
-  __shared__ int cdst[AMAX];
-  __shared__ int glead[AMAX];
-  __shared__ int srt[AMAX];
-  __shared__ float tmpf[AMAX];
-  __shared__ float tmps[AMAX];
+  __shared__ int pairs[AMAX];  // chosen pairs, destination << 10 | A slot
+  __shared__ int srt[AMAX];    // the same in ascending order
   // similarity operands, two buffers each
-  __shared__ __attribute__((aligned(16))) bf16_t Ahi[2 * SAG * SKP];
-  __shared__ __attribute__((aligned(16))) bf16_t Alo[2 * SAG * SKP];
-  __shared__ __attribute__((aligned(16))) bf16_t Bhi[2 * BMAX * SKP];
-  __shared__ __attribute__((aligned(16))) bf16_t Blo[2 * BMAX * SKP];
-  __shared__ float pbv[Z::WC * SAG];
-  __shared__ int pbi[Z::WC * SAG];
-  __shared__ float red[16];
-  __shared__ int ired[16];
-  __shared__ int selc[6 * AD_NT / 64];  // block_top's counts
+  __shared__ __attribute__((aligned(16))) bf16_t Ahi[SIM ? 2 * SAG * SKP : 8];
+  __shared__ __attribute__((aligned(16))) bf16_t Alo[SIM ? 2 * SAG * SKP : 8];
+  __shared__ __attribute__((aligned(16))) bf16_t Bhi[SIM ? 2 * BMAX * SKP : 8];
+  __shared__ __attribute__((aligned(16))) bf16_t Blo[SIM ? 2 * BMAX * SKP : 8];
+  __shared__ float pbv[SIM ? Z::WC * SAG : 1];
+  __shared__ int pbi[SIM ? Z::WC * SAG : 1];
+  __shared__ float red[3][8];
 
   // CLS-attention scores are gathered here and follow the merge; learned
   // scores are computed after the merge from the merged hidden states
   const bool attnP = a.isP && a.prune_rule == 0;
+  const bool router = a.isM && !a.r_fixed;
+  float z = 0.f;
+  if (router) {
+    const float* xc = a.x + (size_t)a.rmap[base] * d;
+    for (int k = tid; k < d; k += AD_NT) z = fmaf(a.router_w[k], xc[k], z);
+  }
   for (int t = tid; t < T; t += AD_NT) {
     keepf[t] = 1;
     szs[t] = a.size[base + t];
@@ -507,151 +506,173 @@ __global__ __launch_bounds__(AD_NT) void adapt_kernel(AdaptArgs a) {
   }
   if (attnP) {
     for (int t = tid; t < T; t += AD_NT) {
-      float s = a.cls_scores[((size_t)i * a.H) * a.tmax + t];
-      for (int h = 1; h < a.H; h++) s = s + a.cls_scores[((size_t)i * a.H + h) * a.tmax + t];
+      // (three heads' scores in flight; a head past H adds nothing)
+      const float* cs = a.cls_scores + (size_t)i * a.H * a.tmax + t;
+      float s = cs[0];
+      for (int h = 1; h < a.H; h += 3) {
+        float v[3];
+#pragma unroll
+        for (int u = 0; u < 3; u++) v[u] = cs[(size_t)min(h + u, a.H - 1) * a.tmax];
+#pragma unroll
+        for (int u = 0; u < 3; u++) s = h + u < a.H ? s + v[u] : s;
+      }
       sc[t] = s / (float)a.H;
     }
   }
-  __syncthreads();
+  const int nA = (N + 1) / 2, nB = N / 2;
+  if (!SIM && a.isM) {
+    // best matches computed by similarity_kernel, one workgroup per pass
+    for (int e = tid; e < nA; e += AD_NT) {
+      bestsim[e] = a.sim_v[(size_t)i * AD_SIM_STRIDE + e];
+      best[e] = a.sim_i[(size_t)i * AD_SIM_STRIDE + e];
+    }
+  }
 
   // ---------------------------------------------------------- merge --
   int r = 0;
-  if (a.isM && a.r_fixed) {
-    r = min(max(a.r_fixed[i], 0), N / 2);
-    if (tid == 0 && a.tr_r) a.tr_r[tr_row] = r;
-  } else if (a.isM) {
-    float z = 0.f;
-    const float* xc = a.x + (size_t)prow[0] * d;
-    for (int k = tid; k < d; k += AD_NT) z = fmaf(a.router_w[k], xc[k], z);
-    z = bsum(z, red) + a.router_b[0];
+  if (router) {
+    z = bsum(z, red[0]) + a.router_b[0];
     const float m = 1.0f / (1.0f + expf(-z));
     r = merge_count(m, a.rho, a.r_b, N, a.merge_rule);
     if (tid == 0) {
       if (a.tr_r) a.tr_r[tr_row] = r;
       if (a.tr_m) a.tr_m[tr_row] = m;
     }
+  } else {
+    if (a.isM) {
+      r = min(max(a.r_fixed[i], 0), N / 2);
+      if (tid == 0 && a.tr_r) a.tr_r[tr_row] = r;
+    }
+    __syncthreads();
   }
-  const int nA = (N + 1) / 2, nB = N / 2;
   if (r > 0) {
-    if (a.sim_v) {
-      // best matches computed by similarity_kernel, one workgroup per pass
-      for (int e = tid; e < nA; e += AD_NT) {
-        bestsim[e] = a.sim_v[(size_t)i * AMAX + e];
-        best[e] = a.sim_i[(size_t)i * AMAX + e];
-      }
-      __syncthreads();
-    } else {
+    if (SIM)
       similarity_argmax<Z>(a.x, prow, d, nA, nB, rn, bestsim, best, Ahi, Alo, Bhi, Blo, pbv,
                            pbi);
-    }
-    // top-r of A by best similarity, ties to the lower A slot: a radix
-    // selection for many candidates (nA <= AD_NT), else the rank count with
-    // P adjacent lanes splitting the comparisons of one element
-    if (nA > SEL_RADIX_MIN) {
-      const bool ok = tid < nA;
-      bool ch, unused;
-      block_top<1>(order_key(ok ? bestsim[tid] : 0.f), ok, 0u, false, r, ch, unused, selc);
-      if (ok) chosen[tid] = ch;
-    } else {
-      const int P = rank_lanes(nA), p = tid % P;
-      for (int e0 = 0; e0 < nA; e0 += AD_NT / P) {
-        const int aa = e0 + tid / P;
-        int rank = 0;
-        if (aa < nA) {
-          const float v = bestsim[aa];
-          for (int a2 = p; a2 < nA; a2 += P) {
-            const float v2 = bestsim[a2];
-            rank += (v2 > v) || (v2 == v && a2 < aa);
-          }
-        }
-        for (int o = 1; o < P; o <<= 1) rank += __shfl_xor(rank, o, 64);
-        if (aa < nA && p == 0) chosen[aa] = rank < r;
-      }
-    }
-    __syncthreads();
-    // chosen sources in ascending A slot: clist[0 .. r)
-    block_compact(tid < nA && chosen[tid], tid, clist, ired);
-    // destination of each, and the sources sorted by (destination, A slot):
-    // srt[0 .. r) lists the positions q in clist; the sources of one
-    // destination form a group, contiguous in srt and in ascending A slot.
-    // Groups are merged independently.
-    for (int q = tid; q < r; q += AD_NT) cdst[q] = best[clist[q]];
-    __syncthreads();
+    // top-r of A by best similarity, ties to the lower A slot
     {
-      const int P = rank_lanes(r), p = tid % P;
-      for (int e0 = 0; e0 < r; e0 += AD_NT / P) {
-        const int q = e0 + tid / P;
-        int rank = 0;
-        if (q < r) {
-          const int key = cdst[q];
-          for (int q2 = p; q2 < r; q2 += P) {
-            const int k2 = cdst[q2];
-            rank += (k2 < key) || (k2 == key && q2 < q);
+      const int wide = nA > SEL_WAVE_MIN;
+      const int npad = wide ? (nA + 63) & ~63 : (nA + 3) & ~3;  // <= AMAX <= AD_NT
+      if (tid < npad) keys[tid] = tid < nA ? order_key(bestsim[tid]) : 0u;
+    }
+    __syncthreads();
+    // the chosen pairs, in any order
+    if (AMAX > SEL_WAVE_MIN && nA > SEL_WAVE_MIN) {
+      unsigned long long sel[AMAX / 64];
+      wave_top<AMAX / 64>(keys, nA, r, sel);
+      int at = 0;
+#pragma unroll
+      for (int j = 0; j < AMAX / 64; j++) {
+        if (wave == j && (sel[j] >> lane & 1)) {
+          pairs[at + (int)__popcll(sel[j] & ((1ull << lane) - 1ull))] = best[tid] << 10 | tid;
+          keepf[1 + 2 * tid] = 0;
+        }
+        at += (int)__popcll(sel[j]);
+      }
+    } else {
+      // P adjacent lanes split the comparisons of one token (nA P <= AD_NT:
+      // one round)
+      const int P = rank_lanes(nA), p = tid & (P - 1), aa = tid / P;
+      int rank = 0;
+      if (aa < nA) rank = rank_of(keys, nA, aa, keys[aa], p, P);
+      rank = lanes_sum(rank, P);
+      if (aa < nA && p == 0 && rank < r) {
+        pairs[rank] = best[aa] << 10 | aa;
+        keepf[1 + 2 * aa] = 0;
+      }
+    }
+    __syncthreads();
+    // sorted: the sources of one destination form a group, contiguous in srt
+    // and in ascending A slot.  Groups are merged independently.
+    {
+      const int P = rank_lanes(r), p = tid & (P - 1), q = tid / P;
+      int rank = 0, key = 0;
+      if (q < r) {
+        key = pairs[q];
+#pragma unroll 4
+        for (int q2 = p; q2 < r; q2 += P) rank += pairs[q2] < key;
+      }
+      rank = lanes_sum(rank, P);
+      if (q < r && p == 0) srt[rank] = key;
+    }
+    __syncthreads();
+    // size-weighted merge into each receiving destination: a half wave per
+    // group, its lanes at 16-byte pieces f, f + 32, f + 64 of the rows, the
+    // sources SU at a time, so that their loads are in flight together (many
+    // sources can share a destination: one load after the other took up to
+    // 20,000 cycles at 577 tokens).  A group reads A rows and its own B row.
+    constexpr int FU = 3, SU = 4, HW = AD_NT / 32;
+    const int hw = tid >> 5, hl = tid & 31, d4 = d / 4;
+    float4* x4 = (float4*)a.x;
+    for (int q = hw; q < r; q += HW) {
+      const int bb = srt[q] >> 10, a0 = srt[q] & 1023;
+      if (q > 0 && srt[q - 1] >> 10 == bb) continue;
+      const int tb = 2 + 2 * bb, ta0 = 1 + 2 * a0;
+      float4* xb4 = x4 + (size_t)prow[tb] * d4;
+      const float4* xa4 = x4 + (size_t)prow[ta0] * d4;
+      const float sb = szs[tb], sa0 = szs[ta0];
+      for (int f0 = hl; f0 - hl < d4; f0 += 32 * FU) {
+        float4 num[FU], xa0[FU];
+#pragma unroll
+        for (int u = 0; u < FU; u++) {
+          const int f = min(f0 + 32 * u, d4 - 1);
+          num[u] = xb4[f];
+          xa0[u] = xa4[f];
+        }
+#pragma unroll
+        for (int u = 0; u < FU; u++) {
+          num[u] = make_float4(sb * num[u].x, sb * num[u].y, sb * num[u].z, sb * num[u].w);
+          num[u].x = num[u].x + sa0 * xa0[u].x;
+          num[u].y = num[u].y + sa0 * xa0[u].y;
+          num[u].z = num[u].z + sa0 * xa0[u].z;
+          num[u].w = num[u].w + sa0 * xa0[u].w;
+        }
+        float den = sb + sa0;
+        float s2 = attnP ? sc[tb] + sc[ta0] : 0.f;
+        for (int pp = q + 1; pp < r && srt[pp] >> 10 == bb; pp += SU) {
+          float4 xa[SU][FU];
+          float sa[SU], se[SU];
+          bool in[SU];
+#pragma unroll
+          for (int v = 0; v < SU; v++) {
+            const int pr = srt[min(pp + v, r - 1)], ta = 1 + 2 * (pr & 1023);
+            in[v] = pp + v < r && pr >> 10 == bb;
+            sa[v] = szs[ta];
+            se[v] = attnP ? sc[ta] : 0.f;
+            const float4* xs4 = x4 + (size_t)prow[ta] * d4;
+#pragma unroll
+            for (int u = 0; u < FU; u++) xa[v][u] = xs4[min(f0 + 32 * u, d4 - 1)];
+          }
+#pragma unroll
+          for (int v = 0; v < SU; v++) {
+            if (!in[v]) break;
+#pragma unroll
+            for (int u = 0; u < FU; u++) {
+              num[u].x = num[u].x + sa[v] * xa[v][u].x;
+              num[u].y = num[u].y + sa[v] * xa[v][u].y;
+              num[u].z = num[u].z + sa[v] * xa[v][u].z;
+              num[u].w = num[u].w + sa[v] * xa[v][u].w;
+            }
+            den = den + sa[v];
+            s2 = s2 + se[v];
           }
         }
-        for (int o = 1; o < P; o <<= 1) rank += __shfl_xor(rank, o, 64);
-        if (q < r && p == 0) srt[rank] = q;
+#pragma unroll
+        for (int u = 0; u < FU; u++)
+          if (f0 + 32 * u < d4)
+            xb4[f0 + 32 * u] =
+                make_float4(num[u].x / den, num[u].y / den, num[u].z / den, num[u].w / den);
+        if (f0 + 32 * FU >= d4 + hl && hl == 0) {  // the group's last pieces
+          a.size[base + tb] = den;
+          if (attnP) sc[tb] = s2;
+        }
       }
     }
-    __syncthreads();
-    const bool start = tid < r && (tid == 0 || cdst[srt[tid]] != cdst[srt[tid - 1]]);
-    const int ng = block_compact(start, tid, glead, ired);  // glead[k]: first position of group k
-    // size-weighted merge into each receiving destination (16-byte pieces);
-    // the destination row and the group's first source are loaded together
-    const int d4 = d / 4;
-    float4* x4 = (float4*)a.x;
-    for (int idx = tid; idx < ng * d4; idx += AD_NT) {
-      const int k = idx / d4, f = idx - k * d4;
-      const int p0 = glead[k], p1 = k + 1 < ng ? glead[k + 1] : r;
-      const int bb = cdst[srt[p0]], a0 = clist[srt[p0]];
-      const size_t rowb = (size_t)prow[2 + 2 * bb];
-      const float4 xb = x4[rowb * d4 + f];
-      const float4 xa0 = x4[(size_t)prow[1 + 2 * a0] * d4 + f];
-      const float sb = szs[2 + 2 * bb], sa0 = szs[1 + 2 * a0];
-      float4 num = make_float4(sb * xb.x, sb * xb.y, sb * xb.z, sb * xb.w);
-      num.x = num.x + sa0 * xa0.x;
-      num.y = num.y + sa0 * xa0.y;
-      num.z = num.z + sa0 * xa0.z;
-      num.w = num.w + sa0 * xa0.w;
-      float den = sb + sa0;
-      for (int pp = p0 + 1; pp < p1; pp++) {
-        const int aa = clist[srt[pp]];
-        const float sa = szs[1 + 2 * aa];
-        const float4 xa = x4[(size_t)prow[1 + 2 * aa] * d4 + f];
-        num.x = num.x + sa * xa.x;
-        num.y = num.y + sa * xa.y;
-        num.z = num.z + sa * xa.z;
-        num.w = num.w + sa * xa.w;
-        den = den + sa;
-      }
-      x4[rowb * d4 + f] = make_float4(num.x / den, num.y / den, num.z / den, num.w / den);
-    }
-    for (int k = tid; k < ng; k += AD_NT) {
-      const int p0 = glead[k], p1 = k + 1 < ng ? glead[k + 1] : r;
-      const int bb = cdst[srt[p0]];
-      float den = szs[2 + 2 * bb];
-      float s2 = attnP ? sc[2 + 2 * bb] : 0.f;
-      for (int pp = p0; pp < p1; pp++) {
-        const int aa = clist[srt[pp]];
-        den = den + szs[1 + 2 * aa];
-        if (attnP) s2 = s2 + sc[1 + 2 * aa];
-      }
-      tmpf[k] = den;
-      tmps[k] = s2;
-    }
-    __syncthreads();
-    for (int k = tid; k < ng; k += AD_NT) {
-      const int bb = cdst[srt[glead[k]]];
-      a.size[base + 2 + 2 * bb] = tmpf[k];
-      if (attnP) sc[2 + 2 * bb] = tmps[k];
-    }
-    for (int q = tid; q < r; q += AD_NT) {
-      const int aa = clist[q];
-      keepf[1 + 2 * aa] = 0;
-      if (a.tr_merge) {
-        const int so = a.origin[base + 1 + 2 * aa];
+    if (a.tr_merge) {
+      for (int q = tid; q < r; q += AD_NT) {
+        const int so = a.origin[base + 1 + 2 * (srt[q] & 1023)];
         if (so >= 0 && so <= a.n0)
-          a.tr_merge[tr_row * (a.n0 + 1) + so] = a.origin[base + 2 + 2 * best[aa]];
+          a.tr_merge[tr_row * (a.n0 + 1) + so] = a.origin[base + 2 + 2 * (srt[q] >> 10)];
       }
     }
     __syncthreads();
@@ -663,10 +684,10 @@ __global__ __launch_bounds__(AD_NT) void adapt_kernel(AdaptArgs a) {
     const float* lg = a.head_buf + (size_t)i * a.C;
     float lm = -INFINITY;
     for (int k = tid; k < a.C; k += AD_NT) lm = fmaxf(lm, lg[k]);
-    lm = bmax(lm, red);
+    lm = bmax(lm, red[1]);
     float s = 0.f;
     for (int k = tid; k < a.C; k += AD_NT) s += expf(lg[k] - lm);
-    s = bsum(s, red);
+    s = bsum(s, red[2]);
     const float c = 1.0f / s;
     fire = (a.delta < 1.0f) && (c >= a.delta);
     if (tid == 0 && a.tr_c) a.tr_c[tr_row] = c;
@@ -679,74 +700,72 @@ __global__ __launch_bounds__(AD_NT) void adapt_kernel(AdaptArgs a) {
   // ----------------------------------------------------------- prune --
   if (a.isP && !fire && a.prune_rule == 1) {
     // s_t = w . z_t + beta on the merged rows (Eq. 8): one half wave per
-    // token, 16-byte pieces, fixed-order half-wave sum.  The merge's row
-    // writes above are visible here: same workgroup, past a barrier.
+    // token, 16-byte pieces, fixed-order half-wave sum, the rows of RU tokens
+    // loaded together.  The merge's row writes above are visible here: same
+    // workgroup, past a barrier.
+    constexpr int RU = 4, HW = AD_NT / 32;
     const int hw = tid >> 5, hl = tid & 31, d4 = d >> 2;
     const float4* w4 = (const float4*)a.prune_w;
     const float pb = a.prune_b[0];
-    for (int t = 1 + hw; t < T; t += AD_NT / 32) {
-      if (!keepf[t]) continue;
-      const float4* xr = (const float4*)(a.x + (size_t)prow[t] * d);
-      float s = 0.f;
-      for (int q = hl; q < d4; q += 32) {
-        const float4 v = xr[q], w = w4[q];
-        s = fmaf(v.x, w.x, s);
-        s = fmaf(v.y, w.y, s);
-        s = fmaf(v.z, w.z, s);
-        s = fmaf(v.w, w.w, s);
+    for (int t0 = 1 + hw; t0 < T; t0 += RU * HW) {
+      const float4* xr[RU];
+      float s[RU];
+#pragma unroll
+      for (int u = 0; u < RU; u++) {
+        xr[u] = (const float4*)(a.x + (size_t)prow[min(t0 + u * HW, T - 1)] * d);
+        s[u] = 0.f;
       }
-      s = half_sum(s);
-      if (hl == 0) sc[t] = s + pb;
+#pragma unroll 3
+      for (int q = hl; q < d4; q += 32) {
+        const float4 w = w4[q];
+#pragma unroll
+        for (int u = 0; u < RU; u++) {
+          const float4 v = xr[u][q];
+          s[u] = fmaf(v.x, w.x, s[u]);
+          s[u] = fmaf(v.y, w.y, s[u]);
+          s[u] = fmaf(v.z, w.z, s[u]);
+          s[u] = fmaf(v.w, w.w, s[u]);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < RU; u++) {
+        const float v = half_sum(s[u]);
+        if (hl == 0 && t0 + u * HW < T) sc[t0 + u * HW] = v + pb;
+      }
     }
     __syncthreads();
   }
+  int kept = T - r;  // rows kept: all but the merged sources, or the pruned ones
   if (a.isP && !fire) {
-    int ns = 0;
-    for (int t = 1 + tid; t < T; t += AD_NT) ns += keepf[t];
-    ns = bsum_i(ns, ired);
-    const int k = (int)floor(__dmul_rn(a.tau_eff, (double)ns));
-    // top-k of the kept patch tokens by score, ties to the lower slot: a
-    // radix selection for many candidates (patch token t = 1 + e,
-    // T - 1 <= 2 AD_NT), else the rank count with P adjacent lanes
-    // splitting the comparisons of one token
-    if (T - 1 > SEL_RADIX_MIN) {
-      const int t0 = 1 + tid, t1 = 1 + AD_NT + tid;
-      const bool ok0 = t0 < T && keepf[t0], ok1 = t1 < T && keepf[t1];
-      bool ch0, ch1;
-      block_top<2>(order_key(ok0 ? sc[t0] : 0.f), ok0, order_key(ok1 ? sc[t1] : 0.f), ok1, k,
-                   ch0, ch1, selc);
-      if (t0 < T) knew[t0] = ch0;
-      if (t1 < T) knew[t1] = ch1;
-    } else {
-      const int P = rank_lanes(T - 1), p = tid % P;
-      for (int e0 = 0; e0 < T - 1; e0 += AD_NT / P) {
-        const int t = 1 + e0 + tid / P;
-        const bool act = t < T && keepf[t];
-        int rank = 0;
-        if (act) {
-          const float v = sc[t];
-          for (int t2 = 1 + p; t2 < T; t2 += P) {
-            const float v2 = sc[t2];
-            rank += keepf[t2] & ((v2 > v) | (v2 == v && t2 < t));
-          }
-        }
-        for (int o = 1; o < P; o <<= 1) rank += __shfl_xor(rank, o, 64);
-        if (t < T && p == 0) knew[t] = act && rank < k;
-      }
-    }
+    const int k = (int)floor(__dmul_rn(a.tau_eff, (double)(N - r)));
+    kept = 1 + k;
+    // top-k of the kept patch tokens t = 1 + e by score, ties to the lower
+    // slot (N <= 2 AD_NT)
+    const bool wide = TMAX > SEL_WAVE_MIN && N > SEL_WAVE_MIN;
+    const int npad = wide ? (N + 63) & ~63 : (N + 3) & ~3;  // <= TMAX
+    for (int e = tid; e < npad; e += AD_NT)
+      keys[e] = e < N && keepf[1 + e] ? order_key(sc[1 + e]) : 0u;
     __syncthreads();
-    for (int t = 1 + tid; t < T; t += AD_NT) keepf[t] = knew[t];
+    if (wide) {
+      unsigned long long sel[TMAX / 64];
+      wave_top<TMAX / 64>(keys, N, k, sel);
+#pragma unroll
+      for (int j = 0; j < TMAX / 64; j++)
+        if ((j & 7) == wave && 64 * j + lane < N) keepf[1 + 64 * j + lane] = (sel[j] >> lane) & 1;
+    } else {
+      const int P = rank_lanes(N), p = tid & (P - 1);
+      const int e = tid / P;
+      const unsigned key = e < N ? keys[e] : 0u;
+      int rank = 0;
+      if (key) rank = rank_of(keys, N, e, key, p, P);
+      rank = lanes_sum(rank, P);
+      if (e < N && p == 0) keepf[1 + e] = key && rank < k;
+    }
     __syncthreads();
   }
 
-  int cnt = 0;
-  for (int t = tid; t < T; t += AD_NT) {
-    const int kf = fire ? 0 : keepf[t];
-    a.keep[base + t] = kf;
-    cnt += kf;
-  }
-  cnt = bsum_i(cnt, ired);
-  if (tid == 0) a.newlen[i] = cnt;
+  for (int t = tid; t < T; t += AD_NT) a.keep[base + t] = fire ? 0 : keepf[t];
+  if (tid == 0) a.newlen[i] = fire ? 0 : kept;
 }
 
 // Best matches of the merge step for long samples, one workgroup per (live
@@ -773,21 +792,18 @@ __global__ __launch_bounds__(AD_NT) void similarity_kernel(AdaptArgs a) {
   __shared__ int pbi[Z::WC * SAG];
   for (int t = threadIdx.x; t < T; t += AD_NT) prow[t] = a.rmap[base + t];
   __syncthreads();
-  similarity_argmax<Z>(a.x, prow, a.d, nA, nB, rn, a.sim_v + (size_t)i * Z::AMAX,
-                       a.sim_i + (size_t)i * Z::AMAX, Ahi, Alo, Bhi, Blo, pbv, pbi,
+  similarity_argmax<Z>(a.x, prow, a.d, nA, nB, rn, a.sim_v + (size_t)i * AD_SIM_STRIDE,
+                       a.sim_i + (size_t)i * AD_SIM_STRIDE, Ahi, Alo, Bhi, Blo, pbv, pbi,
                        pass * SAG, 1);
 }
 
 hipError_t launch_adapt(const AdaptArgs& a, hipStream_t s) {
   if (a.nlive_ub <= 0) return hipSuccess;
-  AdaptArgs one = a;  // single-pass classes: the adapt kernel computes the matches itself
-  one.sim_v = nullptr;
-  one.sim_i = nullptr;
   if (a.T_ub <= 128 && a.d % AdSize<128>::SKC == 0) {
-    adapt_kernel<AdSize<128>><<<a.nlive_ub, AD_NT, 0, s>>>(one);
+    adapt_kernel<AdSize<128>, true><<<a.nlive_ub, AD_NT, 0, s>>>(a);
   } else if (a.T_ub <= 256) {
     if (a.d % AdSize<256>::SKC != 0) return hipErrorInvalidValue;
-    adapt_kernel<AdSize<256>><<<a.nlive_ub, AD_NT, 0, s>>>(one);
+    adapt_kernel<AdSize<256>, true><<<a.nlive_ub, AD_NT, 0, s>>>(a);
   } else {
     typedef AdSize<AD_TMAX> Z;
     // the split similarity: passes of 128 A rows (8 waves as 4 groups of 32
@@ -796,16 +812,16 @@ hipError_t launch_adapt(const AdaptArgs& a, hipStream_t s) {
     typedef AdSize<AD_TMAX, 2> ZS;
     static_assert(ZS::AMAX == Z::AMAX, "one match stride for both kernels");
     if (a.T_ub > AD_TMAX || a.d % Z::SKC != 0) return hipErrorInvalidValue;
-    AdaptArgs b = a;
-    if (a.isM && a.sim_v && a.sim_i) {
+    if (a.isM && !(a.sim_v && a.sim_i)) {
+      adapt_kernel<Z, true><<<a.nlive_ub, AD_NT, 0, s>>>(a);
+      return hipGetLastError();
+    }
+    if (a.isM) {
       // several passes of A rows: one workgroup each
       const int passes = (a.T_ub / 2 + ZS::SAG - 1) / ZS::SAG;
       similarity_kernel<ZS><<<dim3(a.nlive_ub, passes), AD_NT, 0, s>>>(a);
-    } else {
-      b.sim_v = nullptr;
-      b.sim_i = nullptr;
     }
-    adapt_kernel<Z><<<a.nlive_ub, AD_NT, 0, s>>>(b);
+    adapt_kernel<Z, false><<<a.nlive_ub, AD_NT, 0, s>>>(a);
   }
   return hipGetLastError();
 }
@@ -831,30 +847,32 @@ __global__ __launch_bounds__(256) void compact_kernel(CompactArgs a) {
   __shared__ int ired[8];
   __shared__ int dsts[AD_TMAX / 8], prow[AD_TMAX / 8];  // packed slot (-1: dropped), physical row
 
+  // offset of this sample's rows and its place among the kept samples; for
+  // workgroup (0, 0) the totals instead
+  const bool first = i == 0 && part == 0;
+  const int lim = first ? nl : i;
   int off = 0, j = 0;
-  if (i > 0) {
-    for (int t = tid; t < i; t += 256) {
-      const int n = a.newlen[t];
-      off += n;
-      j += n > 0;
-    }
-    off = block_sum256_i(off, ired);
-    j = block_sum256_i(j, ired);
+  for (int t = tid; t < lim; t += 256) {
+    const int n = a.newlen[t];
+    off += n;
+    j += n > 0;
   }
-  if (i == 0 && part == 0) {
-    int tot = 0, nn = 0;
-    for (int t = tid; t < nl; t += 256) {
-      const int n = a.newlen[t];
-      tot += n;
-      nn += n > 0;
-    }
-    tot = block_sum256_i(tot, ired);
-    nn = block_sum256_i(nn, ired);
+  off = wave_sum_i(off);
+  j = wave_sum_i(j);
+  if (lane == 0) {
+    ired[tid >> 6] = off;
+    ired[4 + (tid >> 6)] = j;
+  }
+  __syncthreads();
+  off = ired[0] + ired[1] + ired[2] + ired[3];
+  j = ired[4] + ired[5] + ired[6] + ired[7];
+  if (first) {
     if (tid == 0) {
-      a.cnt2->nlive = nn;
-      a.cnt2->M = tot;
-      a.cu2[nn] = tot;
+      a.cnt2->nlive = j;
+      a.cnt2->M = off;
+      a.cu2[j] = off;
     }
+    off = j = 0;
   }
   if (i >= nl || a.newlen[i] == 0) return;
   const int base = a.cu[i], Tn = a.cu[i + 1] - base;

@@ -64,30 +64,47 @@ __device__ __forceinline__ float sum_xor32(float v) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+// Value of lane ^ O for O = 1, 2, 4, 8 by DPP moves within 16-lane rows (a
+// few cycles each, where __shfl_xor is a round trip through the LDS unit).
+template <int O>
+__device__ __forceinline__ int lane_xor_i(int v) {
+  static_assert(O == 1 || O == 2 || O == 4 || O == 8, "within a 16-lane row");
+  if (O == 1) return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);   // quad_perm [1, 0, 3, 2]
+  if (O == 2) return __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);   // quad_perm [2, 3, 0, 1]
+  if (O == 8) return __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, true);  // row_ror 8
+  // row_shl 4 into the even quads, row_shr 4 into the odd ones
+  return __builtin_amdgcn_update_dpp(
+      __builtin_amdgcn_update_dpp(v, v, 0x104, 0xF, 0x5, false), v, 0x114, 0xF, 0xA, false);
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
-__device__ __forceinline__ int wave_sum_i(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+template <int O>
+__device__ __forceinline__ float lane_xor(float v) {
+  return __int_as_float(lane_xor_i<O>(__float_as_int(v)));
 }
 
-// Block-wide integer sum for blockDim.x == 256 (4 waves); `red` holds >= 4 ints.
-__device__ __forceinline__ int block_sum256_i(int v, int* red) {
-  v = wave_sum_i(v);
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  __syncthreads();
-  if (l == 0) red[w] = v;
-  __syncthreads();
-  return red[0] + red[1] + red[2] + red[3];
+// Wave-wide reductions over lane ^ 32, 16, 8, 4, 2, 1 in this order.
+__device__ __forceinline__ float wave_sum(float v) {
+  v = sum_xor16(sum_xor32(v));
+  v += lane_xor<8>(v);
+  v += lane_xor<4>(v);
+  v += lane_xor<2>(v);
+  return v + lane_xor<1>(v);
+}
+__device__ __forceinline__ float wave_max(float v) {
+  v = max_xor16(max_xor32(v));
+  v = fmaxf(v, lane_xor<8>(v));
+  v = fmaxf(v, lane_xor<4>(v));
+  v = fmaxf(v, lane_xor<2>(v));
+  return fmaxf(v, lane_xor<1>(v));
+}
+__device__ __forceinline__ int wave_sum_i(int v) {
+  const auto a = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+  v = (int)(a[0] + a[1]);
+  const auto b = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+  v = (int)(b[0] + b[1]);
+  v += lane_xor_i<8>(v);
+  v += lane_xor_i<4>(v);
+  v += lane_xor_i<2>(v);
+  return v + lane_xor_i<1>(v);
 }
 
 // Sum over the 32 lanes of a half wave (lanes 0-31 or 32-63) without LDS

@@ -316,6 +316,7 @@ MERGE_CASES = [
     ([1, 2, 3, 18, 129, 197, 256, 65], 384),  # T <= 256
     ([577, 300, 1, 2, 451], 384),             # T <= 640
     ([197, 5, 66, 31], 192),
+    ([130, 257, 258, 260, 40], 768),          # 128 / 129 / 130 A tokens, wide rows
 ]
 
 
@@ -526,6 +527,39 @@ def test_topk_compact_exact_ties(torch_cuda, lengths):
         rows = np.concatenate([[0], 1 + kept])
         p, q = o["cu"][i], o["cu"][i + 1]
         assert np.array_equal(o["rows"][p:q], cu[i] + rows), i
+
+
+@pytest.mark.parametrize("lengths", [[128, 127, 66], [256, 130, 129, 65], [640, 258, 257, 130, 129]])
+@pytest.mark.parametrize("H,keep", [(1, 0.5), (2, 1.0), (4, 0.02), (12, 0.9)])
+def test_topk_selection_edges(torch_cuda, lengths, H, keep):
+    """Selection sizes around the wave width and the change from the rank
+    count to the wave search (129 tokens), with few distinct scores, equal
+    scores throughout and infinities: the kept sets are identical to the
+    lower-slot tie rule."""
+    torch = torch_cuda
+    print(f"[topk edges] T={lengths} H={H} keep={keep}", flush=True)
+    rng = np.random.default_rng(H + lengths[0])
+    cu = _offsets(lengths)
+    M, B, tmax = int(cu[-1]), len(lengths), max(lengths)
+    x = rng.standard_normal((M, 64)).astype(np.float32)
+    origin = np.concatenate([np.arange(T) for T in lengths]).astype(np.int32)
+    for kind in ("few", "equal", "inf"):
+        S = rng.integers(1, 4, size=(B, 1, tmax)).astype(np.float32) / 8
+        if kind == "equal":
+            S[:] = 0.25
+        if kind == "inf":
+            S[rng.random(S.shape) < 0.2] = np.inf
+            S[rng.random(S.shape) < 0.2] = -np.inf
+        S = np.repeat(S, H, axis=1)  # equal heads: their mean is exact for these values
+        T_ = torch.from_numpy
+        o, _, _, _ = _kern().topk_compact(T_(x).cuda(), T_(np.ones(M, np.float32)).cuda(),
+                                          T_(origin).cuda(), cu, keep, scores=T_(S).cuda(), heads=H)
+        o = {k: v.cpu().numpy() for k, v in o.items()}
+        for i, T in enumerate(lengths):
+            k = int(np.floor(keep * (T - 1)))
+            order = np.argsort(-S[i, 0, 1:T], kind="stable")[:k]
+            rows = np.concatenate([[0], 1 + np.sort(order)])
+            assert np.array_equal(o["origin"][o["cu"][i]:o["cu"][i + 1]], rows), (kind, i)
 
 
 def test_topk_compact_learned_scorer_fp32_ln(torch_cuda):
