@@ -229,7 +229,9 @@ FUSION_API int fusion_profile_read(fusion_model* m, int k, double* total_ms,
  * batch is 1 .. 65536.  Arguments are checked on the host before anything is
  * enqueued (FUSION_E_INVALID_ARG, nothing launched).  Calls with scratch
  * (all but fusion_test_gemm) allocate it for the call and synchronise the
- * stream before returning; fusion_test_gemm is asynchronous.
+ * stream before returning; fusion_test_gemm is asynchronous.  Their _ws
+ * variants at the end take the scratch from the caller and are asynchronous
+ * too.
  * ------------------------------------------------------------------------ */
 
 /* Ragged token state of a batch (all device pointers but cu). */
@@ -348,6 +350,37 @@ FUSION_API int fusion_test_topk_compact(const fusion_ragged* in, const float* sc
                                         int32_t* exit_block, int precision, const float* ln_g,
                                         const float* ln_b, void* ln_out,
                                         const fusion_packed_out* out, void* stream);
+
+/* The calls above with the scratch supplied by the caller, for programs that
+ * make many of them: same arguments, checks and results, but no allocation
+ * and no synchronisation, the call is ordered on the stream like fusion_run
+ * (allocating and draining took 40 to 80 us a call).  ws: device buffer of
+ * ws_bytes >= fusion_test_workspace_bytes(batch, rows) bytes, 256-byte
+ * aligned, any contents, not used by anything else until the call has
+ * finished on its stream; overlapping calls take a buffer each.  The host
+ * arrays are read before the call returns (past 895 samples, or 447 with
+ * merge counts, it waits for the stream).  Every entry of the outputs is
+ * written: what the descriptions above leave untouched becomes -1 (packed
+ * rows, sizes, ids, offsets and samples past the survivors; merge_dst;
+ * cls_scores past a sample's rows; exit_block of continuing samples), -7
+ * (their logits) or 0 (ln_out past the survivors).  Errors: FUSION_E_CAPACITY
+ * for a small workspace, FUSION_E_HIP while the stream is being captured. */
+FUSION_API size_t fusion_test_workspace_bytes(int batch, int rows);
+FUSION_API int fusion_test_attention_ws(int precision, const void* qkv, const float* size,
+                                        const int32_t* cu, int batch, int heads, int d,
+                                        int prop_attn, void* out, float* cls_scores, int tmax,
+                                        void* ws, size_t ws_bytes, void* stream);
+FUSION_API int fusion_test_merge_ws(const fusion_ragged* in, const int32_t* r, int id_stride,
+                                    int32_t* merge_dst, const fusion_packed_out* out, void* ws,
+                                    size_t ws_bytes, void* stream);
+FUSION_API int fusion_test_topk_compact_ws(const fusion_ragged* in, const float* scores, int heads,
+                                           int tmax, const float* prune_w, const float* prune_b,
+                                           double keep_ratio, const float* exit_logits,
+                                           int classes, float delta, float* logits,
+                                           int32_t* exit_block, int precision, const float* ln_g,
+                                           const float* ln_b, void* ln_out,
+                                           const fusion_packed_out* out, void* ws,
+                                           size_t ws_bytes, void* stream);
 
 /* Message of the last failed call on this thread ("" if none). */
 FUSION_API const char* fusion_last_error(void);

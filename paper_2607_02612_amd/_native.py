@@ -100,6 +100,17 @@ SIGNATURES = [
                                          c_float, c_void_p, c_void_p, c_int, c_void_p,
                                          c_void_p, c_void_p, POINTER(FusionPackedOut),
                                          c_void_p]),
+    ("fusion_test_workspace_bytes", c_size_t, [c_int, c_int]),
+    ("fusion_test_attention_ws", c_int, [c_int, c_void_p, c_void_p, c_void_p, c_int,
+                                         c_int, c_int, c_int, c_void_p, c_void_p, c_int,
+                                         c_void_p, c_size_t, c_void_p]),
+    ("fusion_test_merge_ws", c_int, [POINTER(FusionRagged), c_void_p, c_int, c_void_p,
+                                     POINTER(FusionPackedOut), c_void_p, c_size_t, c_void_p]),
+    ("fusion_test_topk_compact_ws", c_int, [POINTER(FusionRagged), c_void_p, c_int, c_int,
+                                            c_void_p, c_void_p, c_double, c_void_p, c_int,
+                                            c_float, c_void_p, c_void_p, c_int, c_void_p,
+                                            c_void_p, c_void_p, POINTER(FusionPackedOut),
+                                            c_void_p, c_size_t, c_void_p]),
     ("fusion_last_error", c_char_p, []),
 ]
 

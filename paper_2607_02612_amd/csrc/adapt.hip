@@ -835,8 +835,9 @@ hipError_t launch_adapt(const AdaptArgs& a, hipStream_t s) {
 // loads and counts a token's packed slot in their ballots, and a small batch
 // is split into more parts: 13.9 -> 12.9 us per launch for DeiT-S at batch
 // 256, 7.7 -> 5.3 us at batch 1, 14.8 -> 11.0 us for 64 samples at 384 x 384.
-// CP_CHUNKS: wave masks that cover the longest sample.
-template <typename T, int CP_CHUNKS>
+// CP_CHUNKS: wave masks that cover the longest sample; FILL: the entries past
+// the survivors are written as well.
+template <typename T, int CP_CHUNKS, bool FILL>
 __global__ __launch_bounds__(256) void compact_kernel(CompactArgs a) {
   const int i = blockIdx.x, part = blockIdx.y;
   const int nl = a.cnt->nlive;
@@ -844,35 +845,73 @@ __global__ __launch_bounds__(256) void compact_kernel(CompactArgs a) {
   // is live any more (the next block must see nlive = 0, not a stale value).
   if (i >= nl && (i != 0 || part != 0)) return;
   const int tid = threadIdx.x, lane = tid & 63;
-  __shared__ int ired[8];
+  __shared__ int ired[16];
   __shared__ int dsts[AD_TMAX / 8], prow[AD_TMAX / 8];  // packed slot (-1: dropped), physical row
 
   // offset of this sample's rows and its place among the kept samples; for
   // workgroup (0, 0) the totals instead
   const bool first = i == 0 && part == 0;
-  const int lim = first ? nl : i;
-  int off = 0, j = 0;
+  const int lim = first || FILL ? nl : i;
+  int off = 0, j = 0, tot = 0, nn = 0;
   for (int t = tid; t < lim; t += 256) {
     const int n = a.newlen[t];
-    off += n;
-    j += n > 0;
+    if (FILL) {
+      tot += n;
+      nn += n > 0;
+    }
+    if (!FILL || t < i) {
+      off += n;
+      j += n > 0;
+    }
   }
   off = wave_sum_i(off);
   j = wave_sum_i(j);
+  if (FILL) {
+    tot = wave_sum_i(tot);
+    nn = wave_sum_i(nn);
+  }
   if (lane == 0) {
     ired[tid >> 6] = off;
     ired[4 + (tid >> 6)] = j;
+    if (FILL) {
+      ired[8 + (tid >> 6)] = tot;
+      ired[12 + (tid >> 6)] = nn;
+    }
   }
   __syncthreads();
   off = ired[0] + ired[1] + ired[2] + ired[3];
   j = ired[4] + ired[5] + ired[6] + ired[7];
+  if (FILL) {
+    tot = ired[8] + ired[9] + ired[10] + ired[11];
+    nn = ired[12] + ired[13] + ired[14] + ired[15];
+  } else if (first) {
+    tot = off;
+    nn = j;
+    off = j = 0;
+  }
   if (first) {
     if (tid == 0) {
-      a.cnt2->nlive = j;
-      a.cnt2->M = off;
-      a.cu2[j] = off;
+      a.cnt2->nlive = nn;
+      a.cnt2->M = tot;
+      a.cu2[nn] = tot;
     }
-    off = j = 0;
+    if (FILL) {
+      for (int t = nn + 1 + tid; t <= a.B; t += 256) a.cu2[t] = -1;
+      for (int t = nn + tid; t < a.B; t += 256) a.live2[t] = -1;
+    }
+  }
+  if (FILL) {
+    const int wg = i * (int)gridDim.y + part, nwg = (int)(gridDim.x * gridDim.y);
+    for (int t = tot + wg * 256 + tid; t < a.fill_rows; t += nwg * 256) {
+      a.rmap2[t] = -1;
+      a.size2[t] = -1.f;
+      a.origin2[t] = -1;
+    }
+    if (a.ln_out) {
+      const size_t end = (size_t)a.fill_rows * a.d, step = (size_t)nwg * 256 * 4;
+      for (size_t t = (size_t)tot * a.d + (size_t)(wg * 256 + tid) * 4; t < end; t += step)
+        Store4<T>::put((T*)a.ln_out + t, make_float4(0.f, 0.f, 0.f, 0.f));
+    }
   }
   if (i >= nl || a.newlen[i] == 0) return;
   const int base = a.cu[i], Tn = a.cu[i + 1] - base;
@@ -937,10 +976,17 @@ hipError_t launch_compact(const CompactArgs& a, hipStream_t s) {
   // with 8 / more parts: 1 sample of 197 tokens 6.5 / 5.3 us, 64 samples of
   // 577 12.8 / 11.0; 4096 workgroups were slower at 256 samples, 17.0 / 12.9)
   const int parts = std::min((a.n0 + 1 + 7) / 8, std::max(8, 1024 / a.nlive_ub));
-  if (a.n0 + 1 <= 256)
-    compact_kernel<T, 4><<<dim3(a.nlive_ub, parts), 256, 0, s>>>(a);
-  else
-    compact_kernel<T, AD_TMAX / 64><<<dim3(a.nlive_ub, parts), 256, 0, s>>>(a);
+  const dim3 grid(a.nlive_ub, parts);
+  if (a.fill_rows > 0) {
+    if (a.n0 + 1 <= 256)
+      compact_kernel<T, 4, true><<<grid, 256, 0, s>>>(a);
+    else
+      compact_kernel<T, AD_TMAX / 64, true><<<grid, 256, 0, s>>>(a);
+  } else if (a.n0 + 1 <= 256) {
+    compact_kernel<T, 4, false><<<grid, 256, 0, s>>>(a);
+  } else {
+    compact_kernel<T, AD_TMAX / 64, false><<<grid, 256, 0, s>>>(a);
+  }
   return hipGetLastError();
 }
 template hipError_t launch_compact<float>(const CompactArgs&, hipStream_t);

@@ -5,7 +5,8 @@
 // ragged layout (per-sample offsets, merge counts); every argument is checked
 // on the host before anything is enqueued.  The calls that need scratch
 // (identity live and row maps, device copies of the offsets, keep flags)
-// allocate it for the call and synchronise the stream before freeing it.
+// either take it from the caller (the _ws entries, asynchronous) or allocate
+// it for the call and synchronise the stream before freeing it.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -135,21 +136,38 @@ int check_packed_out(const fusion_packed_out* o) {
   return FUSION_OK;
 }
 
-// Copy the offsets (and merge counts) to the scratch, the working sizes,
-// and set the identity maps.
-int prepare(const fusion_ragged* in, const int32_t* r, int M, StepScratch& sc, hipStream_t s) {
-  const int B = in->batch;
-  HIP_TRY(hipMemcpyAsync(sc.cu, in->cu, (size_t)(B + 1) * 4, hipMemcpyHostToDevice, s));
-  if (r) HIP_TRY(hipMemcpyAsync(sc.r, r, (size_t)B * 4, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(sc.size, in->size, (size_t)M * 4, hipMemcpyDeviceToDevice, s));
-  HIP_TRY(launch_step_init(sc.live, B, sc.rmap, M, sc.cnt, s));
+// The caller's workspace of a _ws entry: large enough, 256-byte aligned, and
+// not under graph capture (the offsets and counts are those of the call).
+// `wait` is set for batches whose host arrays are copied rather than passed as
+// a kernel argument: the call then waits until they are read.
+int check_ws(const void* ws, size_t bytes, size_t need, int ints, hipStream_t s, bool* wait) {
+  if (!ws || (uintptr_t)ws % 256) return bad("workspace is null or not 256-byte aligned");
+  if (bytes < need)
+    return api_fail(FUSION_E_CAPACITY, ("the call needs " + std::to_string(need) +
+                                        " bytes of workspace").c_str());
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  HIP_TRY(hipStreamIsCapturing(s, &st));
+  if (st != hipStreamCaptureStatusNone)
+    return api_fail(FUSION_E_HIP, "not available while the stream is being captured");
+  *wait = ints > STEP_HOST_INTS;
   return FUSION_OK;
+}
+
+// Offsets (and merge counts) to the scratch, identity maps, counts; `size`:
+// the working copy of the sizes.
+StepInit step_init(const StepScratch& sc, int B, int M, const float* size, bool r) {
+  StepInit a{};
+  a.live = sc.live; a.rmap = sc.rmap; a.cnt = sc.cnt; a.cu = sc.cu;
+  a.r = r ? sc.r : nullptr;
+  a.size_in = size; a.size_out = sc.size;
+  a.B = B; a.M = M;
+  return a;
 }
 
 template <typename T>
 int compact(const fusion_ragged* in, const StepScratch& sc, int T_ub,
             const float* ln_g, const float* ln_b, void* ln_out,
-            const fusion_packed_out* o, hipStream_t s) {
+            const fusion_packed_out* o, bool fill, hipStream_t s) {
   CompactArgs c{};
   c.x = in->x; c.rmap = sc.rmap; c.size = sc.size; c.origin = in->origin;
   c.cu = sc.cu; c.live = sc.live; c.cnt = sc.cnt; c.keep = sc.keep; c.newlen = sc.newlen;
@@ -158,13 +176,14 @@ int compact(const fusion_ragged* in, const StepScratch& sc, int T_ub,
   c.d = in->d; c.n0 = T_ub - 1; c.B = in->batch; c.b = 1; c.tr_ids = nullptr;
   c.nlive_ub = in->batch;
   c.ln_g = ln_g; c.ln_b = ln_b; c.ln_out = ln_out;
+  c.fill_rows = fill ? in->cu[in->batch] : 0;
   HIP_TRY(launch_compact<T>(c, s));
   return FUSION_OK;
 }
 
 int merge_impl(const fusion_ragged* in, const int32_t* r, int id_stride, int32_t* merge_dst,
                const fusion_packed_out* out, hipStream_t s, char* mem, size_t mem_cap,
-               int* M_out, bool with_sim) {
+               int* M_out, bool with_sim, bool fill = false) {
   int M = 0, T_ub = 0;
   if (int rc = check_ragged(in, &M, &T_ub)) return rc;
   if (int rc = check_packed_out(out)) return rc;
@@ -179,7 +198,9 @@ int merge_impl(const fusion_ragged* in, const int32_t* r, int id_stride, int32_t
   if (!mem) return FUSION_OK;  // sizing pass
   if (step_scratch_bytes(in->batch, M, with_sim) > mem_cap) return bad("scratch too small");
   StepScratch sc = carve(mem, in->batch, M, with_sim);
-  if (int rc = prepare(in, r, M, sc, s)) return rc;
+  StepInit st = step_init(sc, in->batch, M, in->size, true);
+  if (fill && merge_dst) st.fill[0] = {merge_dst, (size_t)in->batch * id_stride, 0xFFFFFFFFu};
+  HIP_TRY(launch_step_init(st, in->cu, r, s));
   AdaptArgs a{};
   a.x = in->x; a.rmap = sc.rmap; a.size = sc.size; a.origin = in->origin;
   a.cu = sc.cu; a.live = sc.live; a.cnt = sc.cnt;
@@ -192,7 +213,89 @@ int merge_impl(const fusion_ragged* in, const int32_t* r, int id_stride, int32_t
   a.sim_v = sc.sim_v; a.sim_i = sc.sim_i;
   a.nlive_ub = in->batch; a.T_ub = T_ub;
   HIP_TRY(launch_adapt(a, s));
-  return compact<float>(in, sc, T_ub, nullptr, nullptr, nullptr, out, s);
+  return compact<float>(in, sc, T_ub, nullptr, nullptr, nullptr, out, fill, s);
+}
+
+int check_attention(int precision, const void* qkv, const float* size, const int32_t* cu,
+                    int batch, int heads, int d, int prop_attn, const void* out,
+                    const float* cls_scores, int tmax, int* M, int* T_ub) {
+  if (precision != 0 && precision != 1) return bad("precision must be 0 (fp32) or 1 (bf16)");
+  if (!qkv || !size || !out) return bad("null buffer");
+  if (heads < 1 || d < 1 || d % heads || d % 4 || d > 768) return bad("bad width or heads");
+  if (prop_attn != 0 && prop_attn != 1) return bad("prop_attn must be 0 or 1");
+  if (int rc = check_offsets(cu, batch, M, T_ub)) return rc;
+  if (cls_scores && tmax < *T_ub) return bad("tmax below the longest sample");
+  if (precision == 1 && d / heads != 64) return bad("the bf16 attention kernels need 64-wide heads");
+  return FUSION_OK;
+}
+
+int attention_impl(int precision, const void* qkv, const float* size, const int32_t* cu, int batch,
+                   int heads, int d, int prop_attn, void* out, float* cls_scores, int tmax, int M,
+                   int T_ub, char* mem, bool fill, hipStream_t s) {
+  const int dh = d / heads;
+  StepScratch sc = carve(mem, batch, M);
+  StepInit st = step_init(sc, batch, M, nullptr, false);
+  if (fill && cls_scores)
+    st.fill[0] = {cls_scores, (size_t)batch * heads * tmax, 0xBF800000u};  // -1.0f
+  HIP_TRY(launch_step_init(st, cu, nullptr, s));
+  AttnArgs a{};
+  a.qkv = qkv; a.size = size; a.cu = sc.cu; a.live = sc.live; a.cnt = sc.cnt;
+  a.H = heads; a.dh = dh; a.d = d; a.scale = (float)(1.0 / std::sqrt((double)dh));
+  a.prop_attn = prop_attn; a.out = out; a.cls_scores = cls_scores; a.tmax = tmax;
+  a.token_counts = nullptr; a.L = 1; a.b0 = 0; a.nlive_ub = batch; a.T_ub = T_ub;
+  hipError_t err = precision == 1 ? launch_attention<bf16_t>(a, s) : launch_attention<float>(a, s);
+  if (err != hipSuccess) return hip_fail("launch_attention", err);
+  return FUSION_OK;
+}
+
+int check_topk(const fusion_ragged* in, const float* scores, int heads, int tmax,
+               const float* prune_w, const float* prune_b, double keep_ratio,
+               const float* exit_logits, int classes, float delta, const float* logits,
+               const int32_t* exit_block, int precision, const float* ln_g, const float* ln_b,
+               const void* ln_out, const fusion_packed_out* out, int* M, int* T_ub) {
+  if (int rc = check_ragged(in, M, T_ub)) return rc;
+  if (int rc = check_packed_out(out)) return rc;
+  if (!scores && !(prune_w && prune_b)) return bad("give CLS-attention scores or a learned scorer");
+  if (scores && (heads < 1 || heads > 64 || tmax < *T_ub)) return bad("bad score layout");
+  if (!(keep_ratio >= 0.0 && keep_ratio <= 1.0)) return bad("keep ratio outside [0, 1]");
+  if (exit_logits) {
+    if (classes < 1 || !logits || !exit_block) return bad("exit check needs classes, logits and exit_block");
+    if (!(delta >= 0.f && delta <= 1.f)) return bad("threshold outside [0, 1]");
+  }
+  if (precision != 0 && precision != 1) return bad("precision must be 0 (fp32) or 1 (bf16)");
+  if (ln_out && (!ln_g || !ln_b)) return bad("LayerNorm output needs its gain and bias");
+  return FUSION_OK;
+}
+
+int topk_impl(const fusion_ragged* in, const float* scores, int heads, int tmax,
+              const float* prune_w, const float* prune_b, double keep_ratio,
+              const float* exit_logits, int classes, float delta, float* logits,
+              int32_t* exit_block, int precision, const float* ln_g, const float* ln_b,
+              void* ln_out, const fusion_packed_out* out, int M, int T_ub, char* mem, bool fill,
+              hipStream_t s) {
+  StepScratch sc = carve(mem, in->batch, M);
+  StepInit st = step_init(sc, in->batch, M, in->size, false);
+  if (fill && exit_logits) {
+    st.fill[0] = {logits, (size_t)in->batch * classes, 0xC0E00000u};  // -7.0f
+    st.fill[1] = {exit_block, (size_t)in->batch, 0xFFFFFFFFu};
+  }
+  HIP_TRY(launch_step_init(st, in->cu, nullptr, s));
+  AdaptArgs a{};
+  a.x = in->x; a.rmap = sc.rmap; a.size = sc.size; a.origin = in->origin;
+  a.cu = sc.cu; a.live = sc.live; a.cnt = sc.cnt;
+  a.d = in->d; a.H = scores ? heads : 1; a.n0 = T_ub - 1; a.C = exit_logits ? classes : 0;
+  a.L = 1; a.B = in->batch; a.b = 1;
+  a.isM = 0; a.isE = exit_logits ? 1 : 0; a.isP = 1;
+  a.prune_rule = scores ? FUSION_PRUNE_CLS_ATTN : FUSION_PRUNE_LEARNED;
+  a.prune_w = prune_w; a.prune_b = prune_b;
+  a.head_buf = exit_logits; a.delta = exit_logits ? delta : 1.0f;
+  a.logits = logits; a.exit_block = exit_block;
+  a.cls_scores = scores; a.tmax = tmax; a.tau_eff = keep_ratio;
+  a.keep = sc.keep; a.newlen = sc.newlen;
+  a.nlive_ub = in->batch; a.T_ub = T_ub;
+  HIP_TRY(launch_adapt(a, s));
+  if (precision == 1) return compact<bf16_t>(in, sc, T_ub, ln_g, ln_b, ln_out, out, fill, s);
+  return compact<float>(in, sc, T_ub, ln_g, ln_b, ln_out, out, fill, s);
 }
 
 // Device address of `scratch` on the current device, looked up on the
@@ -249,32 +352,41 @@ FUSION_API int fusion_test_gemm(int precision, const void* A, int lda, const voi
   return FUSION_OK;
 }
 
+FUSION_API size_t fusion_test_workspace_bytes(int batch, int rows) {
+  if (batch < 1 || batch > 65536 || rows < 1) return 0;
+  return step_scratch_bytes(batch, rows, true);
+}
+
 FUSION_API int fusion_test_attention(int precision, const void* qkv, const float* size,
                                      const int32_t* cu, int batch, int heads, int d,
                                      int prop_attn, void* out, float* cls_scores, int tmax,
                                      void* stream) {
-  if (precision != 0 && precision != 1) return bad("precision must be 0 (fp32) or 1 (bf16)");
-  if (!qkv || !size || !out) return bad("null buffer");
-  if (heads < 1 || d < 1 || d % heads || d % 4 || d > 768) return bad("bad width or heads");
-  if (prop_attn != 0 && prop_attn != 1) return bad("prop_attn must be 0 or 1");
-  int M = 0, T_ub = 0;
-  if (int rc = check_offsets(cu, batch, &M, &T_ub)) return rc;
-  if (cls_scores && tmax < T_ub) return bad("tmax below the longest sample");
-  const int dh = d / heads;
-  if (precision == 1 && dh != 64) return bad("the bf16 attention kernels need 64-wide heads");
   hipStream_t s = (hipStream_t)stream;
+  int M = 0, T_ub = 0;
+  if (int rc = check_attention(precision, qkv, size, cu, batch, heads, d, prop_attn, out,
+                               cls_scores, tmax, &M, &T_ub))
+    return rc;
   CallScratch mem(s);
   HIP_TRY(mem.alloc(step_scratch_bytes(batch, M)));
-  StepScratch sc = carve(mem.p, batch, M);
-  HIP_TRY(hipMemcpyAsync(sc.cu, cu, (size_t)(batch + 1) * 4, hipMemcpyHostToDevice, s));
-  HIP_TRY(launch_step_init(sc.live, batch, sc.rmap, M, sc.cnt, s));
-  AttnArgs a{};
-  a.qkv = qkv; a.size = size; a.cu = sc.cu; a.live = sc.live; a.cnt = sc.cnt;
-  a.H = heads; a.dh = dh; a.d = d; a.scale = (float)(1.0 / std::sqrt((double)dh));
-  a.prop_attn = prop_attn; a.out = out; a.cls_scores = cls_scores; a.tmax = tmax;
-  a.token_counts = nullptr; a.L = 1; a.b0 = 0; a.nlive_ub = batch; a.T_ub = T_ub;
-  hipError_t err = precision == 1 ? launch_attention<bf16_t>(a, s) : launch_attention<float>(a, s);
-  if (err != hipSuccess) return hip_fail("launch_attention", err);
+  return attention_impl(precision, qkv, size, cu, batch, heads, d, prop_attn, out, cls_scores,
+                        tmax, M, T_ub, mem.p, false, s);
+}
+
+FUSION_API int fusion_test_attention_ws(int precision, const void* qkv, const float* size,
+                                        const int32_t* cu, int batch, int heads, int d,
+                                        int prop_attn, void* out, float* cls_scores, int tmax,
+                                        void* ws, size_t ws_bytes, void* stream) {
+  hipStream_t s = (hipStream_t)stream;
+  int M = 0, T_ub = 0;
+  bool wait = false;
+  if (int rc = check_attention(precision, qkv, size, cu, batch, heads, d, prop_attn, out,
+                               cls_scores, tmax, &M, &T_ub))
+    return rc;
+  if (int rc = check_ws(ws, ws_bytes, step_scratch_bytes(batch, M), batch + 1, s, &wait)) return rc;
+  if (int rc = attention_impl(precision, qkv, size, cu, batch, heads, d, prop_attn, out,
+                              cls_scores, tmax, M, T_ub, (char*)ws, true, s))
+    return rc;
+  if (wait) HIP_TRY(hipStreamSynchronize(s));
   return FUSION_OK;
 }
 
@@ -288,6 +400,22 @@ FUSION_API int fusion_test_merge(const fusion_ragged* in, const int32_t* r, int 
   const size_t need = step_scratch_bytes(in->batch, M, true);
   HIP_TRY(mem.alloc(need));
   return merge_impl(in, r, id_stride, merge_dst, out, s, mem.p, need, &M, true);
+}
+
+FUSION_API int fusion_test_merge_ws(const fusion_ragged* in, const int32_t* r, int id_stride,
+                                    int32_t* merge_dst, const fusion_packed_out* out, void* ws,
+                                    size_t ws_bytes, void* stream) {
+  hipStream_t s = (hipStream_t)stream;
+  int M = 0;
+  bool wait = false;
+  if (int rc = merge_impl(in, r, id_stride, merge_dst, out, s, nullptr, 0, &M, true)) return rc;
+  if (int rc = check_ws(ws, ws_bytes, step_scratch_bytes(in->batch, M, true), 2 * in->batch + 1, s,
+                        &wait))
+    return rc;
+  if (int rc = merge_impl(in, r, id_stride, merge_dst, out, s, (char*)ws, ws_bytes, &M, true, true))
+    return rc;
+  if (wait) HIP_TRY(hipStreamSynchronize(s));
+  return FUSION_OK;
 }
 
 FUSION_API int fusion_test_merge_noalloc(const fusion_ragged* in, const int32_t* r,
@@ -317,39 +445,42 @@ FUSION_API int fusion_test_topk_compact(const fusion_ragged* in, const float* sc
                                         int32_t* exit_block, int precision, const float* ln_g,
                                         const float* ln_b, void* ln_out,
                                         const fusion_packed_out* out, void* stream) {
-  int M = 0, T_ub = 0;
-  if (int rc = check_ragged(in, &M, &T_ub)) return rc;
-  if (int rc = check_packed_out(out)) return rc;
-  if (!scores && !(prune_w && prune_b)) return bad("give CLS-attention scores or a learned scorer");
-  if (scores && (heads < 1 || heads > 64 || tmax < T_ub)) return bad("bad score layout");
-  if (!(keep_ratio >= 0.0 && keep_ratio <= 1.0)) return bad("keep ratio outside [0, 1]");
-  if (exit_logits) {
-    if (classes < 1 || !logits || !exit_block) return bad("exit check needs classes, logits and exit_block");
-    if (!(delta >= 0.f && delta <= 1.f)) return bad("threshold outside [0, 1]");
-  }
-  if (precision != 0 && precision != 1) return bad("precision must be 0 (fp32) or 1 (bf16)");
-  if (ln_out && (!ln_g || !ln_b)) return bad("LayerNorm output needs its gain and bias");
   hipStream_t s = (hipStream_t)stream;
+  int M = 0, T_ub = 0;
+  if (int rc = check_topk(in, scores, heads, tmax, prune_w, prune_b, keep_ratio, exit_logits,
+                          classes, delta, logits, exit_block, precision, ln_g, ln_b, ln_out, out,
+                          &M, &T_ub))
+    return rc;
   CallScratch mem(s);
   HIP_TRY(mem.alloc(step_scratch_bytes(in->batch, M)));
-  StepScratch sc = carve(mem.p, in->batch, M);
-  if (int rc = prepare(in, nullptr, M, sc, s)) return rc;
-  AdaptArgs a{};
-  a.x = in->x; a.rmap = sc.rmap; a.size = sc.size; a.origin = in->origin;
-  a.cu = sc.cu; a.live = sc.live; a.cnt = sc.cnt;
-  a.d = in->d; a.H = scores ? heads : 1; a.n0 = T_ub - 1; a.C = exit_logits ? classes : 0;
-  a.L = 1; a.B = in->batch; a.b = 1;
-  a.isM = 0; a.isE = exit_logits ? 1 : 0; a.isP = 1;
-  a.prune_rule = scores ? FUSION_PRUNE_CLS_ATTN : FUSION_PRUNE_LEARNED;
-  a.prune_w = prune_w; a.prune_b = prune_b;
-  a.head_buf = exit_logits; a.delta = exit_logits ? delta : 1.0f;
-  a.logits = logits; a.exit_block = exit_block;
-  a.cls_scores = scores; a.tmax = tmax; a.tau_eff = keep_ratio;
-  a.keep = sc.keep; a.newlen = sc.newlen;
-  a.nlive_ub = in->batch; a.T_ub = T_ub;
-  HIP_TRY(launch_adapt(a, s));
-  if (precision == 1) return compact<bf16_t>(in, sc, T_ub, ln_g, ln_b, ln_out, out, s);
-  return compact<float>(in, sc, T_ub, ln_g, ln_b, ln_out, out, s);
+  return topk_impl(in, scores, heads, tmax, prune_w, prune_b, keep_ratio, exit_logits, classes,
+                   delta, logits, exit_block, precision, ln_g, ln_b, ln_out, out, M, T_ub, mem.p,
+                   false, s);
+}
+
+FUSION_API int fusion_test_topk_compact_ws(const fusion_ragged* in, const float* scores, int heads,
+                                           int tmax, const float* prune_w, const float* prune_b,
+                                           double keep_ratio, const float* exit_logits,
+                                           int classes, float delta, float* logits,
+                                           int32_t* exit_block, int precision, const float* ln_g,
+                                           const float* ln_b, void* ln_out,
+                                           const fusion_packed_out* out, void* ws,
+                                           size_t ws_bytes, void* stream) {
+  hipStream_t s = (hipStream_t)stream;
+  int M = 0, T_ub = 0;
+  bool wait = false;
+  if (int rc = check_topk(in, scores, heads, tmax, prune_w, prune_b, keep_ratio, exit_logits,
+                          classes, delta, logits, exit_block, precision, ln_g, ln_b, ln_out, out,
+                          &M, &T_ub))
+    return rc;
+  if (int rc = check_ws(ws, ws_bytes, step_scratch_bytes(in->batch, M), in->batch + 1, s, &wait))
+    return rc;
+  if (int rc = topk_impl(in, scores, heads, tmax, prune_w, prune_b, keep_ratio, exit_logits,
+                         classes, delta, logits, exit_block, precision, ln_g, ln_b, ln_out, out, M,
+                         T_ub, (char*)ws, true, s))
+    return rc;
+  if (wait) HIP_TRY(hipStreamSynchronize(s));
+  return FUSION_OK;
 }
 
 }  // extern "C"

@@ -152,13 +152,34 @@ struct CompactArgs {
   const float* ln_g;
   const float* ln_b;
   void* ln_out;
+  // optional (every sample of the batch live): the outputs have fill_rows
+  // rows, and the entries past the surviving rows and samples are set too, to
+  // -1 (rmap2, size2, origin2, cu2, live2) and 0 (ln_out)
+  int fill_rows;
 };
 template <typename T>
 hipError_t launch_compact(const CompactArgs& a, hipStream_t s);
 
-// Scratch of the kernel-level entry points: live map and row map set to the
-// identity, live counts (nlive = B, M rows).
-hipError_t launch_step_init(int* live, int B, int* rmap, int M, LiveCounts* cnt,
+// Start of a kernel-level call: live map and row map set to the identity, live
+// counts (nlive = B, M rows), the offsets (cu) and merge counts (r, may be
+// null) brought to the device, the working copy of the sizes (size_in may be
+// null), and up to STEP_FILLS output buffers set to a 32-bit pattern.
+constexpr int STEP_FILLS = 2;
+struct StepInit {
+  int* live;
+  int* rmap;
+  LiveCounts* cnt;
+  int* cu;
+  int* r;
+  const float* size_in;
+  float* size_out;
+  int B, M;
+  struct { void* p; size_t n; uint32_t v; } fill[STEP_FILLS];
+};
+// Largest number of offsets and merge counts that travel as an argument of
+// the kernel (all arguments, the hidden ones included, stay under 4 KiB).
+constexpr int STEP_HOST_INTS = 896;
+hipError_t launch_step_init(const StepInit& a, const int32_t* cu_host, const int32_t* r_host,
                             hipStream_t s);
 
 // Error channel of the C ABI (message returned by fusion_last_error).

@@ -3,6 +3,9 @@
 // diagnostic state copy.
 #include "kernels.h"
 
+#include <algorithm>
+#include <cstring>
+
 namespace fusion {
 
 __global__ void init_kernel(float* __restrict__ x, int* __restrict__ rmap,
@@ -208,26 +211,57 @@ template hipError_t launch_pool_ln<bf16_t>(const float*, const int*, const float
                                            const LiveCounts*, const float*, const float*,
                                            bf16_t*, int, int, hipStream_t);
 
-__global__ void step_init_kernel(int* __restrict__ live, int B, int* __restrict__ rmap, int M,
-                                 LiveCounts* cnt) {
-  const int n = B > M ? B : M;
-  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
-    if (t < B) live[t] = t;
-    if (t < M) rmap[t] = t;
-    if (t == 0) {
-      cnt->nlive = B;
-      cnt->M = M;
-    }
+// The host's offsets and merge counts are an argument of the kernel where they
+// fit (one launch instead of up to three copies, which also wait for pageable
+// memory to be staged); a longer batch copies them.
+template <int N> struct HostInts { int32_t v[N]; };
+template <int N>
+__global__ __launch_bounds__(256) void step_init_kernel(StepInit a, HostInts<N> h) {
+  const size_t t0 = (size_t)blockIdx.x * 256 + threadIdx.x, step = (size_t)gridDim.x * 256;
+  for (size_t t = t0; t < (size_t)a.M; t += step) {
+    a.rmap[t] = (int)t;
+    if (a.size_in) a.size_out[t] = a.size_in[t];
   }
+  for (size_t t = t0; t < (size_t)a.B; t += step) a.live[t] = (int)t;
+  if (N > 1) {
+    for (size_t t = t0; t <= (size_t)a.B; t += step) a.cu[t] = h.v[t];
+    if (a.r)
+      for (size_t t = t0; t < (size_t)a.B; t += step) a.r[t] = h.v[a.B + 1 + t];
+  }
+  if (t0 == 0) {
+    a.cnt->nlive = a.B;
+    a.cnt->M = a.M;
+  }
+#pragma unroll
+  for (int k = 0; k < STEP_FILLS; k++)
+    for (size_t t = t0; t < a.fill[k].n; t += step) ((uint32_t*)a.fill[k].p)[t] = a.fill[k].v;
 }
 
-hipError_t launch_step_init(int* live, int B, int* rmap, int M, LiveCounts* cnt,
+hipError_t launch_step_init(const StepInit& a, const int32_t* cu_host, const int32_t* r_host,
                             hipStream_t s) {
-  const int n = B > M ? B : M;
-  int blocks = (n + 255) / 256;
-  if (blocks > 4096) blocks = 4096;
-  if (blocks < 1) blocks = 1;
-  step_init_kernel<<<blocks, 256, 0, s>>>(live, B, rmap, M, cnt);
+  size_t n = (size_t)std::max(a.B + 1, a.M);
+  for (const auto& f : a.fill) n = std::max(n, f.n);
+  const int blocks = (int)std::min<size_t>((n + 255) / 256, 2048);
+  const int ints = a.B + 1 + (a.r ? a.B : 0);
+  auto fill = [&](auto& h) {
+    std::memcpy(h.v, cu_host, (size_t)(a.B + 1) * 4);
+    if (a.r) std::memcpy(h.v + a.B + 1, r_host, (size_t)a.B * 4);
+  };
+  if (ints <= 128) {
+    HostInts<128> h;
+    fill(h);
+    step_init_kernel<128><<<blocks, 256, 0, s>>>(a, h);
+  } else if (ints <= STEP_HOST_INTS) {
+    HostInts<STEP_HOST_INTS> h;
+    fill(h);
+    step_init_kernel<STEP_HOST_INTS><<<blocks, 256, 0, s>>>(a, h);
+  } else {
+    hipError_t e = hipMemcpyAsync(a.cu, cu_host, (size_t)(a.B + 1) * 4, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess && a.r)
+      e = hipMemcpyAsync(a.r, r_host, (size_t)a.B * 4, hipMemcpyHostToDevice, s);
+    if (e != hipSuccess) return e;
+    step_init_kernel<1><<<blocks, 256, 0, s>>>(a, HostInts<1>{});
+  }
   return hipGetLastError();
 }
 

@@ -3,7 +3,9 @@ include/fusion.h): argument marshalling only.  Tensors are passed as device
 pointers; the per-sample row offsets and merge counts are host arrays.
 
 Each function runs one step of the pipeline with the library's HIP kernels
-on caller-supplied packed ragged buffers and returns device tensors.
+on caller-supplied packed ragged buffers and returns device tensors, ordered
+on the current stream.  The scratch of a call is a tensor of torch's caching
+allocator, so a call neither allocates device memory nor waits for the stream.
 """
 from __future__ import annotations
 
@@ -30,6 +32,17 @@ def _host_i32(a):
 
 def _stream():
     return torch.cuda.current_stream().cuda_stream
+
+
+def _workspace(B, M, dev, *used):
+    """Scratch for one call; `used` are the tensors that the current stream
+    reads from now on (they may belong to another one)."""
+    s = torch.cuda.current_stream()
+    for t in used:
+        if t is not None:
+            t.record_stream(s)
+    n = _native.lib().fusion_test_workspace_bytes(B, M)
+    return torch.empty(max(n, 256), dtype=torch.uint8, device=dev), n, s.cuda_stream
 
 
 def _need(t, name, dtype):
@@ -72,13 +85,14 @@ def attention(qkv, size, cu, heads, prop_attn=True, cls_tmax=None):
     if M != cu_h[-1] or size.shape[0] != M:
         raise ValueError("rows do not match the offsets")
     d = d3 // 3
-    out = torch.zeros(M, d, dtype=qkv.dtype, device=qkv.device)
+    out = torch.empty(M, d, dtype=qkv.dtype, device=qkv.device)
     cls = None
     if cls_tmax is not None:
-        cls = torch.full((B, heads, cls_tmax), -1.0, device=qkv.device)
-    check(_native.lib().fusion_test_attention(prec, qkv.data_ptr(), size.data_ptr(), cu_p, B,
-                                              heads, d, int(bool(prop_attn)), out.data_ptr(),
-                                              _ptr(cls), cls_tmax or 0, _stream()))
+        cls = torch.empty((B, heads, cls_tmax), device=qkv.device)
+    ws, n, s = _workspace(B, M, qkv.device, qkv, size)
+    check(_native.lib().fusion_test_attention_ws(prec, qkv.data_ptr(), size.data_ptr(), cu_p, B,
+                                                 heads, d, int(bool(prop_attn)), out.data_ptr(),
+                                                 _ptr(cls), cls_tmax or 0, ws.data_ptr(), n, s))
     return out, cls
 
 
@@ -94,13 +108,15 @@ def _ragged(x, size, origin, cu):
     return rg, cu_h
 
 
-def _packed(M, B, dev):
-    o = dict(rows=torch.full((M,), -1, dtype=torch.int32, device=dev),
-             size=torch.full((M,), -1.0, device=dev),
-             origin=torch.full((M,), -1, dtype=torch.int32, device=dev),
-             cu=torch.full((B + 1,), -1, dtype=torch.int32, device=dev),
-             live=torch.full((B,), -1, dtype=torch.int32, device=dev),
-             counts=torch.full((2,), -1, dtype=torch.int32, device=dev))
+def _packed(M, B, dev, fill=False):
+    """Output buffers; `fill`: for an entry point that leaves the entries past
+    the survivors as they are."""
+    def buf(n, dtype=torch.int32):
+        return torch.full((n,), -1, dtype=dtype, device=dev) if fill else \
+            torch.empty((n,), dtype=dtype, device=dev)
+
+    o = dict(rows=buf(M), size=buf(M, torch.float32), origin=buf(M), cu=buf(B + 1), live=buf(B),
+             counts=buf(2))
     po = FusionPackedOut(*(o[k].data_ptr() for k in ("rows", "size", "origin", "cu", "live",
                                                      "counts")))
     return o, po
@@ -115,10 +131,17 @@ def merge(x, size, origin, cu, r, id_stride, noalloc=False):
     r_h, r_p = _host_i32(r)
     if len(r_h) != B:
         raise ValueError("one merge count per sample")
-    o, po = _packed(x.shape[0], B, x.device)
-    md = torch.full((B, id_stride), -1, dtype=torch.int32, device=x.device)
-    fn = _native.lib().fusion_test_merge_noalloc if noalloc else _native.lib().fusion_test_merge
-    check(fn(byref(rg), r_p, id_stride, md.data_ptr(), byref(po), _stream()))
+    M, dev = x.shape[0], x.device
+    o, po = _packed(M, B, dev, fill=noalloc)
+    if noalloc:
+        md = torch.full((B, id_stride), -1, dtype=torch.int32, device=dev)
+        check(_native.lib().fusion_test_merge_noalloc(byref(rg), r_p, id_stride, md.data_ptr(),
+                                                      byref(po), _stream()))
+        return o, md
+    md = torch.empty((B, id_stride), dtype=torch.int32, device=dev)
+    ws, n, s = _workspace(B, M, dev, x, size, origin)
+    check(_native.lib().fusion_test_merge_ws(byref(rg), r_p, id_stride, md.data_ptr(), byref(po),
+                                             ws.data_ptr(), n, s))
     return o, md
 
 
@@ -140,17 +163,19 @@ def topk_compact(x, size, origin, cu, keep_ratio, scores=None, heads=1, prune_w=
     if exit_logits is not None:
         _need(exit_logits, "exit_logits", torch.float32)
         C = exit_logits.shape[1]
-        logits = torch.full((B, C), -7.0, device=dev)
-        exit_block = torch.full((B,), -1, dtype=torch.int32, device=dev)
+        logits = torch.empty((B, C), device=dev)
+        exit_block = torch.empty((B,), dtype=torch.int32, device=dev)
     ln_out = None
     ln_g = ln_b = None
     if ln is not None:
         ln_g, ln_b = ln
-        ln_out = torch.zeros(M, d, dtype=torch.bfloat16 if precision == 1 else torch.float32,
+        ln_out = torch.empty(M, d, dtype=torch.bfloat16 if precision == 1 else torch.float32,
                              device=dev)
     o, po = _packed(M, B, dev)
-    check(_native.lib().fusion_test_topk_compact(
+    ws, n, s = _workspace(B, M, dev, x, size, origin, scores, exit_logits, prune_w, prune_b, ln_g,
+                          ln_b)
+    check(_native.lib().fusion_test_topk_compact_ws(
         byref(rg), _ptr(scores), heads, tmax, _ptr(prune_w), _ptr(prune_b), c_double(keep_ratio),
         _ptr(exit_logits), C, c_float(delta), _ptr(logits), _ptr(exit_block), precision,
-        _ptr(ln_g), _ptr(ln_b), _ptr(ln_out), byref(po), _stream()))
+        _ptr(ln_g), _ptr(ln_b), _ptr(ln_out), byref(po), ws.data_ptr(), n, s))
     return o, logits, exit_block, ln_out

@@ -195,6 +195,30 @@ def test_kernel_level_entry_points_reject_bad_arguments_on_host():
                                         None, None, 1, None, None, None, br(po), None) == -1
 
 
+def test_workspace_entries_check_arguments_and_workspace_on_host():
+    """The entries with a caller's workspace make the same argument checks
+    first, then refuse a missing, misaligned or small workspace."""
+    lib = _native.lib()
+    br = ctypes.byref
+    cu, rg, po = _ragged_args([0, 4, 9])
+    r = np.array([1, 2], dtype=np.int32)
+    rp, cp = (a.ctypes.data_as(ctypes.c_void_p) for a in (r, cu))
+    need = lib.fusion_test_workspace_bytes(2, 9)
+    assert need > 0 and lib.fusion_test_workspace_bytes(0, 9) == 0
+    bad_r = np.array([1, 3], dtype=np.int32)
+    assert lib.fusion_test_merge_ws(br(rg), bad_r.ctypes.data_as(ctypes.c_void_p), 8, None, br(po),
+                                    4096, need, None) == -1
+    assert lib.fusion_test_attention_ws(1, 8, 8, cp, 2, 2, 128, 1, 8, 8, 3, 4096, need, None) == -1
+    assert lib.fusion_test_topk_compact_ws(br(rg), 8, 1, 9, None, None, 1.5, None, 0, 1.0, None, None,
+                                           1, None, None, None, br(po), 4096, need, None) == -1
+    for ws, n, code in [(None, need, -1), (4096 + 128, need, -1), (4096, 256, -3)]:
+        assert lib.fusion_test_merge_ws(br(rg), rp, 8, None, br(po), ws, n, None) == code
+        assert lib.fusion_test_attention_ws(1, 8, 8, cp, 2, 2, 128, 1, 8, None, 0, ws, n,
+                                            None) == code
+        assert lib.fusion_test_topk_compact_ws(br(rg), 8, 1, 9, None, None, 0.5, None, 0, 1.0, None,
+                                               None, 1, None, None, None, br(po), ws, n, None) == code
+
+
 def test_noalloc_merge_refuses_oversized_calls_on_host():
     """fusion_test_merge_noalloc returns FUSION_E_CAPACITY when a call would
     need more scratch than the static array holds, before any device call."""

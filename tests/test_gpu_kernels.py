@@ -616,3 +616,81 @@ def test_topk_compact_every_sample_exits(torch_cuda):
     assert list(o["counts"].cpu().numpy()) == [0, 0]
     assert np.all(eb.cpu().numpy() == 1)
     assert np.array_equal(logits.cpu().numpy(), lg)
+
+
+# ------------------------------------------ the caller's workspace variants --
+@pytest.mark.parametrize("B", [1, 63, 64, 128, 447, 448, 895, 896])
+def test_workspace_entries_equal_allocating_ones(torch_cuda, B):
+    """The binding (workspace entries; offsets as a kernel argument of two
+    sizes, or copied) gives what the allocating entries write into buffers
+    that hold the documented values before the call, on a side stream and
+    with the arguments reused right after the call."""
+    import ctypes
+    torch = torch_cuda
+    from paper_2607_02612_amd import _native
+    print(f"[workspace] samples={B}", flush=True)
+    L, kern = _native.lib(), _kern()
+    rng = np.random.default_rng(B)
+    lengths = [int(v) for v in rng.integers(1, 12 if B > 64 else 80, size=B)]
+    cu = _offsets(lengths)
+    M, d, H, C, tmax = int(cu[-1]), 128, 2, 7, max(lengths) + 3
+    f = lambda *s: torch.from_numpy(rng.standard_normal(s).astype(np.float32)).cuda()
+    x, size = f(M, d), torch.from_numpy(rng.integers(1, 4, size=M).astype(np.float32)).cuda()
+    origin = torch.from_numpy(np.concatenate([np.arange(T) for T in lengths]).astype(np.int32)).cuda()
+    r = np.array([(T - 1) // 3 for T in lengths], np.int32)
+    qkv, scores, logits_in = f(M, 3 * d).bfloat16(), f(B, H, tmax).abs(), 3 * f(B, C)
+    ln = (f(d), f(d))
+    cp = lambda a: a.ctypes.data_as(ctypes.c_void_p)
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        cu_b, r_b, xb = cu.copy(), r.copy(), x.clone()
+        at, cls = kern.attention(qkv, size, cu_b, H, True, tmax)
+        om, md = kern.merge(xb, size, origin, cu_b, r_b, tmax)
+        ot, lg, eb, lo = kern.topk_compact(x, size, origin, cu_b, 0.6, scores=scores, heads=H,
+                                           exit_logits=logits_in, delta=0.6, ln=ln)
+        cu_b[:], r_b[:] = -1, -1
+    stream.synchronize()
+    full = lambda v, dt, *s: torch.full(s, v, dtype=dt, device="cuda")
+    i32, f32 = torch.int32, torch.float32
+
+    def packed():
+        o = dict(rows=full(-1, i32, M), size=full(-1, f32, M), origin=full(-1, i32, M),
+                 cu=full(-1, i32, B + 1), live=full(-1, i32, B), counts=full(-1, i32, 2))
+        return o, _native.FusionPackedOut(*(o[k].data_ptr() for k in ("rows", "size", "origin", "cu",
+                                                                      "live", "counts")))
+    s0 = torch.cuda.current_stream().cuda_stream
+    at0, cls0 = full(0, torch.bfloat16, M, d), full(-1, f32, B, H, tmax)
+    _native.check(L.fusion_test_attention(1, qkv.data_ptr(), size.data_ptr(), cp(cu), B, H, d, 1,
+                                          at0.data_ptr(), cls0.data_ptr(), tmax, s0))
+    assert torch.equal(at, at0) and torch.equal(cls, cls0)
+    xa = x.clone()
+    o0, po = packed()
+    md0 = full(-1, i32, B, tmax)
+    rg = _native.FusionRagged(xa.data_ptr(), size.data_ptr(), origin.data_ptr(), cp(cu), B, d)
+    _native.check(L.fusion_test_merge(ctypes.byref(rg), cp(r), tmax, md0.data_ptr(),
+                                      ctypes.byref(po), s0))
+    assert torch.equal(xb, xa) and torch.equal(md, md0)
+    assert all(torch.equal(om[k], o0[k]) for k in o0)
+    o0, po = packed()
+    lg0, eb0, lo0 = full(-7, f32, B, C), full(-1, i32, B), full(0, torch.bfloat16, M, d)
+    rg = _native.FusionRagged(x.data_ptr(), size.data_ptr(), origin.data_ptr(), cp(cu), B, d)
+    _native.check(L.fusion_test_topk_compact(
+        ctypes.byref(rg), scores.data_ptr(), H, tmax, None, None, 0.6, logits_in.data_ptr(), C, 0.6,
+        lg0.data_ptr(), eb0.data_ptr(), 1, ln[0].data_ptr(), ln[1].data_ptr(), lo0.data_ptr(),
+        ctypes.byref(po), s0))
+    assert torch.equal(lg, lg0) and torch.equal(eb, eb0) and torch.equal(lo, lo0)
+    assert all(torch.equal(ot[k], o0[k]) for k in o0)
+
+
+def test_workspace_entries_refuse_capture(torch_cuda):
+    """Offsets and counts belong to one call: no recording into a graph."""
+    torch = torch_cuda
+    from paper_2607_02612_amd import FusionError
+    qkv, size = torch.zeros(4, 192, device="cuda"), torch.ones(4, device="cuda")
+    _kern().attention(qkv, size, [0, 4], 1)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        with pytest.raises(FusionError):
+            _kern().attention(qkv, size, [0, 4], 1)
