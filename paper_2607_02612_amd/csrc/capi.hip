@@ -8,6 +8,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstdio>
 #include <cstring>
 #include <string>
 #include <vector>
@@ -299,6 +300,7 @@ struct fusion_model {
   // runtime parameters
   float delta[FUSION_MAX_LAYERS];  // per exit head
   double rho = 1.0;
+  double router_mid[FUSION_MAX_LAYERS] = {};  // sigmoid of each router's bias
   // profiling
   bool prof = false;
   struct Rec { int kind; hipEvent_t a, b; };
@@ -390,7 +392,7 @@ int run_impl(fusion_model* m, const float* images, int B, float* logits,
     HIP_OR_FAIL(launch_patchify<T>(images, (T*)m->ffn, B, c.in_ch, c.img, c.patch, s));
     Epi e{EPI_PATCH, m->x, d, m->pe_b, nullptr, m->pos, n0};
     HIP_OR_FAIL(launch_gemm<T>((const T*)m->ffn, c.pdim, (const T*)m->pe_w, d, c.pdim,
-                               nullptr, B * n0, B * n0, e, s));
+                               nullptr, B * n0, B * n0, 0, e, s));
   }
   if (o.stop_block > 0 && o.stop_stage == 0) {
     *cur_out = cur;
@@ -398,14 +400,16 @@ int run_impl(fusion_model* m, const float* images, int B, float* logits,
   }
   const float scale = (float)(1.0 / std::sqrt((double)c.dh));
   const double tau_rho = m->rho;
-  int T_ub = T0;
+  // tokens per sample entering a block: the bound, and the number expected
+  // from the merge rule with each router at its bias
+  int T_ub = T0, T_est = T0;
   const fusion_trace* tr = o.trace;
   bool ln1_done = false;  // act already holds this block's LN1 (from the compaction)
   for (int b = 1; b <= L; b++) {
     const BlockW& w = m->blk[b - 1];
     const bool isM = c.merge_mask >> (b - 1) & 1, isE = c.exit_mask >> (b - 1) & 1,
                isP = c.prune_mask >> (b - 1) & 1;
-    const int M_ub = B * T_ub;
+    const int M_ub = B * T_ub, M_est = B * T_est;
     const int* Mdev = &m->cnt[cur]->M;
     if (!ln1_done) {
       Prof p(m, s, K_LN);
@@ -417,7 +421,7 @@ int run_impl(fusion_model* m, const float* images, int B, float* logits,
       Prof p(m, s, K_QKV);
       Epi e{EPI_STORE, m->qkv, 3 * d, w.qkv_b, nullptr, nullptr, 0};
       HIP_OR_FAIL(launch_gemm<T>((const T*)m->act, d, (const T*)w.qkv_w, 3 * d, d, Mdev, 0,
-                                 M_ub, e, s));
+                                 M_ub, M_est, e, s));
     }
     {
       Prof p(m, s, K_ATTN);
@@ -434,7 +438,8 @@ int run_impl(fusion_model* m, const float* images, int B, float* logits,
     {
       Prof p(m, s, K_PROJ);
       Epi e{EPI_RESID, m->x, d, w.proj_b, m->rmap[cur], nullptr, 0};
-      HIP_OR_FAIL(launch_gemm<T>((const T*)m->act, d, (const T*)w.proj_w, d, d, Mdev, 0, M_ub, e, s));
+      HIP_OR_FAIL(launch_gemm<T>((const T*)m->act, d, (const T*)w.proj_w, d, d, Mdev, 0, M_ub,
+                                 M_est, e, s));
     }
     if (o.stop_block == b && o.stop_stage == 1) break;
     {
@@ -445,13 +450,14 @@ int run_impl(fusion_model* m, const float* images, int B, float* logits,
     {
       Prof p(m, s, K_FC1);
       Epi e{EPI_GELU, m->ffn, c.mlp, w.fc1_b, nullptr, nullptr, 0};
-      HIP_OR_FAIL(launch_gemm<T>((const T*)m->act, d, (const T*)w.fc1_w, c.mlp, d, Mdev, 0, M_ub, e, s));
+      HIP_OR_FAIL(launch_gemm<T>((const T*)m->act, d, (const T*)w.fc1_w, c.mlp, d, Mdev, 0, M_ub,
+                                 M_est, e, s));
     }
     {
       Prof p(m, s, K_FC2);
       Epi e{EPI_RESID, m->x, d, w.fc2_b, m->rmap[cur], nullptr, 0};
       HIP_OR_FAIL(launch_gemm<T>((const T*)m->ffn, c.mlp, (const T*)w.fc2_w, d, c.mlp, Mdev, 0,
-                                 M_ub, e, s));
+                                 M_ub, M_est, e, s));
     }
     if (o.stop_block == b && o.stop_stage == 2) break;
     if (isE) {
@@ -469,13 +475,13 @@ int run_impl(fusion_model* m, const float* images, int B, float* logits,
                                         m->cu[cur], m->live[cur], 1, B, nullptr, L, s));
       if (kind == FUSION_EXIT_LINEAR) {
         Epi e{EPI_F32, m->head_buf, c.C, w.eb, nullptr, nullptr, 0};
-        HIP_OR_FAIL(launch_gemm<T>((const T*)m->hc, d, (const T*)w.ew, c.C, d, nl, 0, B, e, s));
+        HIP_OR_FAIL(launch_gemm<T>((const T*)m->hc, d, (const T*)w.ew, c.C, d, nl, 0, B, 0, e, s));
       } else {
         const int hx = c.exit_hidden;
         Epi e1{EPI_GELU, m->hbuf, hx, w.eb1, nullptr, nullptr, 0};
-        HIP_OR_FAIL(launch_gemm<T>((const T*)m->hc, d, (const T*)w.ew1, hx, d, nl, 0, B, e1, s));
+        HIP_OR_FAIL(launch_gemm<T>((const T*)m->hc, d, (const T*)w.ew1, hx, d, nl, 0, B, 0, e1, s));
         Epi e2{EPI_F32, m->head_buf, c.C, w.eb2, nullptr, nullptr, 0};
-        HIP_OR_FAIL(launch_gemm<T>((const T*)m->hbuf, hx, (const T*)w.ew2, c.C, hx, nl, 0, B, e2, s));
+        HIP_OR_FAIL(launch_gemm<T>((const T*)m->hbuf, hx, (const T*)w.ew2, c.C, hx, nl, 0, B, 0, e2, s));
       }
     }
     if (isM || isE || isP) {
@@ -524,7 +530,15 @@ int run_impl(fusion_model* m, const float* images, int B, float* logits,
         ln1_done = b < L;
         cur = nx;
       }
+      if (isM) {
+        const int N = T_est - 1;
+        const double t = c.merge_rule == FUSION_MERGE_FRACTION
+                             ? m->rho * m->router_mid[b - 1] * N * 0.5
+                             : 2.0 * m->rho * m->router_mid[b - 1] * c.r_b[b - 1] + 0.5;
+        T_est -= std::min((int)t, N / 2);
+      }
       if (isP) {
+        T_est = 1 + (int)std::floor(tau_eff * (double)(T_est - 1));
         const int keep_ub = (int)std::floor(tau_eff * (double)(T_ub - 1));
         T_ub = 1 + keep_ub;
       }
@@ -538,7 +552,7 @@ int run_impl(fusion_model* m, const float* images, int B, float* logits,
                                     m->cu[cur], m->live[cur], 1, B, exit_block, L, s));
     Epi e{EPI_F32, logits, c.C, m->head_b, m->live[cur], nullptr, 0};
     HIP_OR_FAIL(launch_gemm<T>((const T*)m->hc, d, (const T*)m->head_w, c.C, d,
-                               &m->cnt[cur]->nlive, 0, B, e, s));
+                               &m->cnt[cur]->nlive, 0, B, 0, e, s));
   }
   return FUSION_OK;
 }
@@ -668,6 +682,14 @@ FUSION_API int fusion_model_create(const void* blob, size_t blob_bytes, int max_
     w.eln_g = F(p + "eln_g"); w.eln_b = F(p + "eln_b"); w.eb = F(p + "eb"); w.ew = Wm(p + "ew");
     w.eb1 = F(p + "eb1"); w.eb2 = F(p + "eb2"); w.ew1 = Wm(p + "ew1"); w.ew2 = Wm(p + "ew2");
     w.prune_w = F(p + "prune_w"); w.prune_b = F(p + "prune_b");
+  }
+  for (size_t k = 0; k < tensors.size(); k++) {
+    int b = 0;
+    if (std::sscanf(tensors[k].name.c_str(), "blk%d.router_b", &b) == 1 &&
+        tensors[k].name == "blk" + std::to_string(b) + ".router_b" && b >= 1 && b <= c.L) {
+      const double v = *(const float*)(host.data() + foff[k]);
+      m->router_mid[b - 1] = std::isnan(v) ? 0.5 : 1.0 / (1.0 + std::exp(-v));
+    }
   }
   // ---- workspace
   const size_t esz = c.precision == 1 ? 2 : 4;

@@ -10,6 +10,7 @@
 // for an upper bound (tiles past M return at once).
 #include "kernels.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace fusion {
@@ -105,8 +106,7 @@ __global__ __launch_bounds__(256) void gemm_valu(const T* __restrict__ A,
 // ------------------------------------------------------------ bf16 MFMA --
 // MBx128 output tile per workgroup (MB = 256: 8 waves in a 4x2 grid; 128: 4
 // waves, 2x2; 64: 2 waves side by side), each wave a 64x64 sub-tile of 2x2
-// v_mfma_f32_32x32x16_bf16 blocks; launches with few 64-row tiles split
-// each into 4 waves of 32x64 (1x2 blocks) instead, which changes no result.
+// v_mfma_f32_32x32x16_bf16 blocks.
 //
 // K is consumed in steps of KSV = 32 through a ring of three LDS stages
 // (64-wide steps with two stages measured slower on every shape, long K
@@ -148,7 +148,6 @@ __global__ __launch_bounds__(256) void gemm_valu(const T* __restrict__ A,
 // element q of lane l is C[8*(q/4) + 4*(l/32) + q%4][l%32].
 constexpr int NB = 128;
 constexpr int NXCD = 8;
-constexpr long THIN_TILES = 768;
 constexpr long F32_TILES64 = 512;
 // 32 x 32 blocks up to which a bf16 launch takes the small-launch kernel
 constexpr long SMALL_TILES = 2048;
@@ -175,13 +174,13 @@ __device__ __forceinline__ void wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
 }
 
-// MB = 256, 128 or 64 rows per tile; each wave owns WR * 32 rows x 64
-// columns (WR = 2: 2 x 2 MFMA blocks, WR = 1: 1 x 2), the waves in a grid of
-// MB / (32 WR) rows x 2 columns.  Every layout accumulates each output
-// element over the same 16-wide K pieces in the same order from the same
-// bias start, so the results do not depend on MB or WR.  KSV = K step (32).
-template <int EPI, int MB, int KSV, int WR>
-__global__ __launch_bounds__(MB / (32 * WR) * 128, MB == 128 ? 3 : 1) void gemm_mfma_bf16(
+// MB = 256, 128 or 64 rows per tile; each wave owns 64 rows x 64 columns (2 x
+// 2 MFMA blocks), the waves in a grid of MB / 64 rows x 2 columns.  Every
+// layout accumulates each output element over the same 16-wide K pieces in
+// the same order from the same bias start, so the results do not depend on
+// MB.  KSV = K step (32).
+template <int EPI, int MB, int KSV>
+__global__ __launch_bounds__(MB * 2, MB == 128 ? 3 : 1) void gemm_mfma_bf16(
     const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W,
     int N, int K, const int* M_dev, int M_host, int n_mt, Epi e) {
   static_assert(KSV == 32, "K step of 32");
@@ -189,8 +188,7 @@ __global__ __launch_bounds__(MB / (32 * WR) * 128, MB == 128 ? 3 : 1) void gemm_
   constexpr int ROWB = KS * 2;                        // bytes per staged row
   constexpr int CPR = KS / 8;                         // 16-byte chunks per staged row
   constexpr int RPI = 64 / CPR;                       // rows per DMA instruction
-  static_assert(WR == 1 || WR == 2, "32 or 64 rows per wave");
-  constexpr int WMR = 32 * WR;                        // rows per wave
+  constexpr int WR = 2, WMR = 32 * WR;                // 32-row blocks and rows per wave
   constexpr int NWV = MB / WMR * 2;                   // waves
   constexpr int NT = NWV * 64;                        // threads
   constexpr int STGB = (MB + NB) * ROWB;              // bytes per stage
@@ -678,13 +676,241 @@ __global__ __launch_bounds__(64 * NWV) void gemm_mfma_bf16_small(
 template <int EPI>
 void launch_small(const bf16_t* A, int lda, const bf16_t* W, int N, int K, const int* M_dev,
                   int M_host, int M_ub, long t32, const Epi& e, hipStream_t s) {
-  const int m32 = (M_ub + 31) / 32, m64 = (M_ub + 63) / 64, n64 = (N + 63) / 64;
+  const int m32 = (M_ub + 31) / 32, m64 = (M_ub + 63) / 64, n32 = (N + 31) / 32, n64 = (N + 63) / 64;
   if (t32 <= 256)
-    gemm_mfma_bf16_small<EPI, 1, 1, 4, 4><<<(int)t32, 256, 0, s>>>(A, lda, W, N, K, M_dev, M_host, e);
+    gemm_mfma_bf16_small<EPI, 1, 1, 4, 4><<<m32 * n32, 256, 0, s>>>(A, lda, W, N, K, M_dev, M_host, e);
   else if (t32 <= 900)
     gemm_mfma_bf16_small<EPI, 1, 2, 4, 4><<<m32 * n64, 256, 0, s>>>(A, lda, W, N, K, M_dev, M_host, e);
   else
     gemm_mfma_bf16_small<EPI, 2, 2, 3, 4><<<m64 * n64, 256, 0, s>>>(A, lda, W, N, K, M_dev, M_host, e);
+}
+
+// ---------------------------------------------- bf16 MFMA, medium launches --
+// Launches whose 64- or 128-row tiles fit the chip once are bound by how fast
+// a CU gets its operands: the three workgroups that share an A panel fetch the
+// same lines, so few distinct bytes are in flight, and 64-byte rows use half
+// of each cache line (197 images, fc2: the K loop without its copies took half
+// the time; without its MFMAs or LDS reads it took all of it).  Here K steps
+// of 64 stage whole 128-byte lines, and 8 waves of BI 32 x 32 blocks (two
+// workgroups a CU, so 16 waves) hide more of each other's latency: the
+// operands of each half step are read while the other half multiplies.  128 x
+// 128 tiles (BI = 2) in two stages, 64 x 128 (BI = 1) in three.  The blocks
+// accumulate the same 16-wide K pieces in the same order from the bias as the
+// other kernels, and the epilogue does the same arithmetic, so results are
+// bit-identical to theirs.  Staged rows are 128 bytes with their eight 16-byte
+// chunks XOR-permuted by row % 8.  Every wave stages its own 32-row blocks
+// through the drained ring, so its output rows are written in 128-byte (fp32)
+// or 64-byte (bf16) pieces without another barrier.
+template <int EPI, int BI, int NSTG>
+__global__ __launch_bounds__(512, 2) void gemm_mfma_bf16_mid(
+    const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W, int N, int K,
+    const int* M_dev, int M_host, int n_mt, Epi e) {
+  constexpr int KS = 64, ROWB = 128, RPI = 8;     // K step, bytes per staged row, rows per DMA
+  constexpr int WM = 2, WN = 4, NWV = WM * WN;    // wave grid
+  constexpr int WR = 32 * BI, MB = WR * WM;       // rows per wave and tile; NB = 32 WN columns
+  constexpr int STGB = (MB + NB) * ROWB;
+  constexpr int DPW = (MB + NB) / RPI / NWV;      // DMA instructions per wave and stage
+  static_assert((MB + NB) / RPI % NWV == 0 && NB == 32 * WN, "stage split");
+  const int M = M_dev ? *M_dev : M_host;
+  const int n_nt = (N + NB - 1) / NB;
+  const int id = blockIdx.x;
+  const int xcd = id % NXCD, local = id / NXCD;
+  const int mt = (local / n_nt) * NXCD + xcd, nt = local % n_nt;
+  const int m0 = mt * MB, n0 = nt * NB;
+  if (mt >= n_mt || m0 >= M) return;
+  __shared__ __attribute__((aligned(16))) char smem[NSTG * STGB];
+  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int wm = wave / WN, wn = wave % WN, hh = lane >> 5, l32 = lane & 31;
+  const int nw = n0 + wn * 32;                    // the wave's first column
+  const bf16_t* sbase[DPW];
+  unsigned voff[DPW], dst[DPW];
+#pragma unroll
+  for (int u = 0; u < DPW; u++) {
+    const int q = wave * DPW + u;
+    const bool isA = q < MB / RPI;
+    const int r = (isA ? q : q - MB / RPI) * RPI + (lane >> 3);
+    const int gr = isA ? min(m0 + r, M - 1) : min(n0 + r, N - 1);
+    sbase[u] = isA ? A : W;
+    voff[u] = (unsigned)(((size_t)gr * (isA ? lda : K) + (((lane & 7) ^ (r & 7)) << 3)) * 2);
+    dst[u] = q * RPI * ROWB;
+  }
+  const int nk = K / KS;
+#pragma unroll
+  for (int st = 0; st < NSTG - 1; st++)
+    if (st < nk) {
+#pragma unroll
+      for (int u = 0; u < DPW; u++) dma16s(sbase[u] + st * KS, voff[u], lds0 + st * STGB + dst[u]);
+    }
+  f32x16_t acc[BI];
+#pragma unroll
+  for (int q4 = 0; q4 < 4; q4++) {
+    const f32x4_t bv = *(const f32x4_t*)(e.bias + min(nw + 8 * q4 + 4 * hh, N - 4));
+#pragma unroll
+    for (int i = 0; i < BI; i++)
+#pragma unroll
+      for (int q = 0; q < 4; q++) acc[i][4 * q4 + q] = bv[q];
+  }
+  bf16x8_t fa[2][2][BI], fb[2][2];
+  auto fetch = [&](auto st_c, auto p_c) {  // half p of the stage in slot ST
+    constexpr int ST = decltype(st_c)::value, p = decltype(p_c)::value;
+    const char* Ab = smem + ST * STGB + (wm * WR + l32) * ROWB;
+    const char* Bb = smem + ST * STGB + (MB + wn * 32 + l32) * ROWB;
+#pragma unroll
+    for (int ks = 0; ks < 2; ks++) {
+      const int c = ((4 * p + 2 * ks + hh) ^ (l32 & 7)) << 4;
+#pragma unroll
+      for (int i = 0; i < BI; i++) fa[p][ks][i] = *(const bf16x8_t*)(Ab + i * 32 * ROWB + c);
+      fb[p][ks] = *(const bf16x8_t*)(Bb + c);
+    }
+  };
+  auto mma = [&](auto p_c) {
+    constexpr int p = decltype(p_c)::value;
+#pragma unroll
+    for (int ks = 0; ks < 2; ks++)
+#pragma unroll
+      for (int i = 0; i < BI; i++)
+        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[p][ks], fa[p][ks][i], acc[i], 0, 0, 0);
+  };
+  auto landed = [&](int kt) {  // stage kt and every earlier one
+    if (kt + NSTG - 2 < nk)
+      wait_vm<DPW * (NSTG - 2)>();
+    else
+      wait_vm<0>();
+    __syncthreads();
+  };
+  // step kt, its first half's operands in registers: stage kt + NSTG - 1 goes
+  // into the slot of step kt - 1, whose operands every wave had read before
+  // the barrier that step kt - 1 ended with
+  typedef std::integral_constant<int, 0> H0;
+  typedef std::integral_constant<int, 1> H1;
+  auto step = [&](int kt, auto st_c) {
+    constexpr int ST = decltype(st_c)::value;
+    if (kt + NSTG - 1 < nk) {
+      constexpr int SN = (ST + NSTG - 1) % NSTG;
+#pragma unroll
+      for (int u = 0; u < DPW; u++)
+        dma16s(sbase[u] + (kt + NSTG - 1) * KS, voff[u], lds0 + SN * STGB + dst[u]);
+    }
+    fetch(st_c, H1{});
+    mma(H0{});
+    if (kt + 1 < nk) {
+      landed(kt + 1);
+      fetch(std::integral_constant<int, (ST + 1) % NSTG>{}, H0{});
+    }
+    mma(H1{});
+  };
+  landed(0);
+  fetch(H0{}, H0{});
+  for (int kt = 0; kt < nk; kt += NSTG) {
+    step(kt, std::integral_constant<int, 0>{});
+    if (kt + 1 < nk) step(kt + 1, std::integral_constant<int, 1>{});
+    if constexpr (NSTG > 2)
+      if (kt + 2 < nk) step(kt + 2, std::integral_constant<int, 2>{});
+  }
+  static_assert(NSTG == 2 || NSTG == 3, "the K loop is unrolled by the stages");
+  __syncthreads();  // the ring is drained
+  if constexpr (EPI == EPI_STORE || EPI == EPI_GELU) {
+    constexpr int SROW = 64 + 16;  // staged bf16 row of 32 columns
+    static_assert(NWV * WR * SROW <= NSTG * STGB, "epilogue staging fits");
+    char* sw = smem + wave * WR * SROW;
+#pragma unroll
+    for (int i = 0; i < BI; i++)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; q4++) {
+        float v0 = acc[i][4 * q4 + 0], v1 = acc[i][4 * q4 + 1];
+        float v2 = acc[i][4 * q4 + 2], v3 = acc[i][4 * q4 + 3];
+        if (EPI == EPI_GELU) {
+          v0 = gelu_erf(v0); v1 = gelu_erf(v1); v2 = gelu_erf(v2); v3 = gelu_erf(v3);
+        }
+        *(uint2*)(sw + (i * 32 + l32) * SROW + q4 * 16 + hh * 8) =
+            make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
+      }
+    // 4 lanes per row
+#pragma unroll
+    for (int k = 0; k < WR / 16; k++) {
+      const int r = (lane >> 2) + 16 * k, n = nw + (lane & 3) * 8, m = m0 + wm * WR + r;
+      const uint4 v = *(const uint4*)(sw + r * SROW + (lane & 3) * 16);
+      if (m < M && n < N) *(uint4*)((bf16_t*)e.out + (size_t)m * e.ldo + n) = v;
+    }
+  } else {
+    constexpr int SROW = 128 + 16;  // staged fp32 row
+    static_assert(NWV * 32 * SROW <= NSTG * STGB, "epilogue staging fits");
+    char* sw = smem + wave * 32 * SROW;
+    const int nc = nw + (lane & 7) * 4, ncc = min(nc, N - 4);  // this lane's columns
+#pragma unroll
+    for (int i = 0; i < BI; i++) {
+      // 8 lanes per row: output rows and addend rows of the lane's 4 pieces
+      float4 xv[4];
+      size_t orow[4];
+      int m[4];
+#pragma unroll
+      for (int k = 0; k < 4; k++) {
+        m[k] = m0 + wm * WR + i * 32 + (lane >> 3) + 8 * k;
+        orow[k] = (size_t)min(m[k], M - 1);
+      }
+      if ((EPI == EPI_RESID || EPI == EPI_F32) && e.rows) {
+#pragma unroll
+        for (int k = 0; k < 4; k++) orow[k] = (size_t)e.rows[orow[k]];
+      }
+#pragma unroll
+      for (int k = 0; k < 4; k++) {
+        if (EPI == EPI_RESID) xv[k] = *(const float4*)((const float*)e.out + orow[k] * e.ldo + ncc);
+        if (EPI == EPI_PATCH) {
+          const int sm = (int)orow[k] / e.n0, pj = (int)orow[k] - sm * e.n0;
+          orow[k] = (size_t)sm * (e.n0 + 1) + 1 + pj;
+          xv[k] = *(const float4*)(e.pos + (size_t)(1 + pj) * e.ldo + ncc);
+        }
+      }
+#pragma unroll
+      for (int q4 = 0; q4 < 4; q4++)
+        *(float4*)(sw + l32 * SROW + q4 * 32 + hh * 16) = make_float4(
+            acc[i][4 * q4], acc[i][4 * q4 + 1], acc[i][4 * q4 + 2], acc[i][4 * q4 + 3]);
+#pragma unroll
+      for (int k = 0; k < 4; k++) {
+        float4 v = *(const float4*)(sw + ((lane >> 3) + 8 * k) * SROW + (lane & 7) * 16);
+        if (EPI != EPI_F32)
+          v = make_float4(v.x + xv[k].x, v.y + xv[k].y, v.z + xv[k].z, v.w + xv[k].w);
+        if (m[k] < M && nc < N) *(float4*)((float*)e.out + orow[k] * e.ldo + nc) = v;
+      }
+    }
+  }
+}
+
+// Medium launches by the number of tiles (two workgroups a CU: 512 at a time;
+// the 3-stage kernel above holds 768 of its 128-row tiles), us per launch on
+// cold operands, 3-stage kernel / this one:
+//   64-row tiles fit once: BI = 1 (384 x 1536 with residual: 2400 rows 18.5 /
+//     13.4, 9000 rows 24.8 / 20.4; 1536 x 384 with GELU: 2400 rows 10.1 / 8.5)
+//   128-row tiles fit once: BI = 2 (384 x 1536: 12608 rows 35.9 / 26.2, 20000
+//     rows 46.9 / 33.1; 768 x 3072: 9456 rows 85.9 / 52.2; 1152 x 384: 6304
+//     rows 14.8 / 10.8; 1536 x 384: 4700 rows 17.7 / 12.5)
+//   up to 768: the 3-stage kernel, which holds them all (384 x 1536: 28000
+//     rows 58.9 / 60.8; 1152 x 384: 9000 rows 15.7 / 16.8)
+//   up to 1024: BI = 2 in two even rounds (384 x 1536: 36928 rows 87.5 / 77.4;
+//     384 x 384: 40000 rows 41.6 / 37.8), not with GELU, whose vector work
+//     prefers three independent workgroups (1536 x 384 inside a pass: 9500
+//     rows 25.4 / 28.0)
+//   up to 1850, plain store only: BI = 2 (2304 x 768: 12608 rows 66.2 / 57.2;
+//     1152 x 384: 20000 rows 28.8 / 26.3, 26000 rows 38.7 / 37.2, but 30000
+//     rows 43.7 / 46.9 in 256-row tiles)
+//   beyond, the 3-stage kernel (384 x 1536: 50432 rows 109.9 / 108.8)
+// Whole passes: 64 images of the Tab. I model 1369 -> 1299 us.
+int mid_blocks(int mode, long t64, long t128) {
+  if (t64 <= 512) return 1;
+  const long most = mode == EPI_GELU ? 512 : mode == EPI_STORE ? 1850 : 1024;
+  if (t128 <= 512 || (t128 > 768 && t128 <= most)) return 2;
+  return 0;
+}
+template <int EPI>
+void launch_mid(int bi, const bf16_t* A, int lda, const bf16_t* W, int N, int K, const int* M_dev,
+                int M_host, int M_ub, const Epi& e, hipStream_t s) {
+  const int n_mt = (M_ub + 64 * bi - 1) / (64 * bi);
+  const int grid = (n_mt + NXCD - 1) / NXCD * NXCD * ((N + NB - 1) / NB);
+  if (bi == 1)
+    gemm_mfma_bf16_mid<EPI, 1, 3><<<grid, 512, 0, s>>>(A, lda, W, N, K, M_dev, M_host, n_mt, e);
+  else
+    gemm_mfma_bf16_mid<EPI, 2, 2><<<grid, 512, 0, s>>>(A, lda, W, N, K, M_dev, M_host, n_mt, e);
 }
 
 // ------------------------------------------------------------ fp32 MFMA --
@@ -818,16 +1044,17 @@ __global__ __launch_bounds__(256) void gemm_mfma_f32(const float* __restrict__ A
 
 template <>
 hipError_t launch_gemm<float>(const float* A, int lda, const float* W, int N,
-                              int K, const int* M_dev, int M_host, int M_ub,
+                              int K, const int* M_dev, int M_host, int M_ub, int M_est,
                               const Epi& e, hipStream_t s) {
   if (M_ub <= 0) return hipSuccess;
+  const int Mx = M_est > 0 ? std::min(M_est, M_ub) : M_ub;
   // matrix cores: whole 16-float K steps, 16-byte aligned operand rows within
   // 32-bit byte offsets; anything else takes the general kernel
   if (K >= 16 && K % 16 == 0 && lda % 4 == 0 && ((uintptr_t)A | (uintptr_t)W) % 16 == 0 &&
       (size_t)M_ub * lda * 4 <= 0xFFFFFFFFull && (size_t)N * K * 4 <= 0xFFFFFFFFull) {
     const int vec = N % 4 == 0 && e.ldo % 4 == 0 &&
                     ((uintptr_t)e.out | (uintptr_t)e.bias | (uintptr_t)e.pos) % 16 == 0;
-    auto tiles = [&](int mb) { return (long)((M_ub + mb - 1) / mb) * ((N + mb - 1) / mb); };
+    auto tiles = [&](int mb) { return (long)((Mx + mb - 1) / mb) * ((N + mb - 1) / mb); };
     auto grid = [&](int mb) {
       return ((M_ub + mb - 1) / mb + NXCD - 1) / NXCD * NXCD * ((N + mb - 1) / mb);
     };
@@ -851,8 +1078,11 @@ hipError_t launch_gemm<float>(const float* A, int lda, const float* W, int N,
 template <>
 hipError_t launch_gemm<bf16_t>(const bf16_t* A, int lda, const bf16_t* W,
                                int N, int K, const int* M_dev, int M_host,
-                               int M_ub, const Epi& e, hipStream_t s) {
+                               int M_ub, int M_est, const Epi& e, hipStream_t s) {
   if (M_ub <= 0) return hipSuccess;
+  // the kernel is chosen for the rows expected, the grid covers the bound
+  // (every kernel gives the same bits)
+  const int Mx = M_est > 0 ? std::min(M_est, M_ub) : M_ub;
   // The K steps need K % 32 == 0 and 16-byte aligned rows; the vector
   // epilogues need N and the output stride to be multiples of 8 (bf16
   // outputs) or 4 (fp32 outputs).  The model creation rejects bf16 shapes
@@ -864,7 +1094,7 @@ hipError_t launch_gemm<bf16_t>(const bf16_t* A, int lda, const bf16_t* W,
     return hipErrorInvalidValue;
   if ((e.mode == EPI_STORE || e.mode == EPI_GELU) && (N % 8 != 0 || e.ldo % 8 != 0))
     return hipErrorInvalidValue;
-  const long t32 = (long)((M_ub + 31) / 32) * ((N + 31) / 32);
+  const long t32 = (long)((Mx + 31) / 32) * ((N + 31) / 32);
   if (K % 64 == 0 && t32 <= SMALL_TILES) {
     switch (e.mode) {
       case EPI_STORE: launch_small<EPI_STORE>(A, lda, W, N, K, M_dev, M_host, M_ub, t32, e, s); break;
@@ -877,30 +1107,39 @@ hipError_t launch_gemm<bf16_t>(const bf16_t* A, int lda, const bf16_t* W,
     return hipGetLastError();
   }
   const int n_nt = (N + NB - 1) / NB;
+  const long t128 = (long)((Mx + 127) / 128) * n_nt;
+  const int bi = K % 64 == 0 ? mid_blocks(e.mode, (long)((Mx + 63) / 64) * n_nt, t128) : 0;
+  if (bi) {
+    switch (e.mode) {
+      case EPI_STORE: launch_mid<EPI_STORE>(bi, A, lda, W, N, K, M_dev, M_host, M_ub, e, s); break;
+      case EPI_GELU: launch_mid<EPI_GELU>(bi, A, lda, W, N, K, M_dev, M_host, M_ub, e, s); break;
+      case EPI_RESID: launch_mid<EPI_RESID>(bi, A, lda, W, N, K, M_dev, M_host, M_ub, e, s); break;
+      case EPI_F32: launch_mid<EPI_F32>(bi, A, lda, W, N, K, M_dev, M_host, M_ub, e, s); break;
+      case EPI_PATCH: launch_mid<EPI_PATCH>(bi, A, lda, W, N, K, M_dev, M_host, M_ub, e, s); break;
+      default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
   // tile rows: 256 (8 waves) when there are enough tiles to fill the CUs
-  // several times over, 64 when 128-row tiles would leave CUs idle
-  const bool small = (long)((M_ub + 127) / 128) * n_nt < 512;
+  // several times over, 64 when 128-row tiles would leave CUs idle (only K
+  // that the medium kernel does not take)
+  const bool small = t128 < 512;
   // K steps of 32 with three stages everywhere: 64-wide steps (two stages,
   // half the barriers) measured slower on every shape here, long K included
   // (not for the GELU epilogue, whose vector work overlaps better with
   // three 4-wave workgroups per CU than with two 8-wave ones)
   const bool big = e.mode != EPI_GELU &&
-                   (long)((M_ub + 255) / 256) * n_nt >= 1024;
+                   (long)((Mx + 255) / 256) * n_nt >= 925;
   const int mb = small ? 64 : big ? 256 : 128;
   const int n_mt = (M_ub + mb - 1) / mb;
   const int grid = (n_mt + NXCD - 1) / NXCD * NXCD * n_nt;
-  // 32-row waves (twice the waves per tile) for 64-row tiles when the
-  // launch has fewer tiles than the CUs hold at once
-  const bool thin = small && (long)n_mt * n_nt < THIN_TILES;
 #define FUSION_GEMM_LAUNCH(E)                                                                    \
-  if (small && thin)                                                                            \
-    gemm_mfma_bf16<E, 64, 32, 1><<<grid, 256, 0, s>>>(A, lda, W, N, K, M_dev, M_host, n_mt, e); \
-  else if (small)                                                                               \
-    gemm_mfma_bf16<E, 64, 32, 2><<<grid, 128, 0, s>>>(A, lda, W, N, K, M_dev, M_host, n_mt, e); \
+  if (small)                                                                               \
+    gemm_mfma_bf16<E, 64, 32><<<grid, 128, 0, s>>>(A, lda, W, N, K, M_dev, M_host, n_mt, e); \
   else if (big)                                                                                 \
-    gemm_mfma_bf16<E, 256, 32, 2><<<grid, 512, 0, s>>>(A, lda, W, N, K, M_dev, M_host, n_mt, e); \
+    gemm_mfma_bf16<E, 256, 32><<<grid, 512, 0, s>>>(A, lda, W, N, K, M_dev, M_host, n_mt, e); \
   else                                                                                          \
-    gemm_mfma_bf16<E, 128, 32, 2><<<grid, 256, 0, s>>>(A, lda, W, N, K, M_dev, M_host, n_mt, e)
+    gemm_mfma_bf16<E, 128, 32><<<grid, 256, 0, s>>>(A, lda, W, N, K, M_dev, M_host, n_mt, e)
   switch (e.mode) {
     case EPI_STORE: FUSION_GEMM_LAUNCH(EPI_STORE); break;
     case EPI_GELU: FUSION_GEMM_LAUNCH(EPI_GELU); break;

@@ -346,8 +346,8 @@ FUSION_API int fusion_test_gemm(int precision, const void* A, int lda, const voi
   hipStream_t s = (hipStream_t)stream;
   hipError_t err =
       precision == 1
-          ? launch_gemm<bf16_t>((const bf16_t*)A, lda, (const bf16_t*)W, N, K, nullptr, M, M, e, s)
-          : launch_gemm<float>((const float*)A, lda, (const float*)W, N, K, nullptr, M, M, e, s);
+          ? launch_gemm<bf16_t>((const bf16_t*)A, lda, (const bf16_t*)W, N, K, nullptr, M, M, 0, e, s)
+          : launch_gemm<float>((const float*)A, lda, (const float*)W, N, K, nullptr, M, M, 0, e, s);
   if (err != hipSuccess) return hip_fail("launch_gemm", err);
   return FUSION_OK;
 }

@@ -27,11 +27,13 @@ struct Epi {
   int n0;           // EPI_PATCH
 };
 
-// Row count: *M_dev when non-null, else M_host.  M_ub bounds the grid.
+// Row count: *M_dev when non-null, else M_host.  M_ub bounds it (the grid);
+// M_est (0: M_ub) is the count expected, for which the kernel is chosen: it
+// decides the speed, never the result.
 template <typename T>
 hipError_t launch_gemm(const T* A, int lda, const T* W, int N, int K,
-                       const int* M_dev, int M_host, int M_ub, const Epi& e,
-                       hipStream_t s);
+                       const int* M_dev, int M_host, int M_ub, int M_est,
+                       const Epi& e, hipStream_t s);
 
 template <typename T>
 hipError_t launch_patchify(const float* img, T* out, int B, int C, int S,

@@ -134,6 +134,47 @@ def test_gemm_bf16_small_launches(torch_cuda, M, N, K, epi):
     assert np.array_equal(run(times).reshape(times, M, N), np.broadcast_to(g, (times, M, N)))
 
 
+@pytest.mark.parametrize("M,N,K,epi", [
+    (2113, 1000, 64, "f32"), (2300, 1004, 192, "resid"), (2561, 840, 128, "store"),
+    (4097, 520, 1536, "gelu"), (5000, 384, 384, "resid"),            # 64-row tiles, three stages
+    (4225, 1000, 64, "store"), (4300, 1004, 192, "f32"), (9000, 520, 128, "gelu"),
+    (12608, 384, 1536, "resid"),                                    # 128-row tiles, two stages
+    (12300, 1000, 64, "gelu"), (33000, 384, 128, "resid"), (25000, 1000, 64, "store"),  # more rounds
+    (300, 384, 96, "resid"), (2500, 1000, 32, "store"),             # K not a multiple of 64
+])
+def test_gemm_bf16_medium_launches(torch_cuda, M, N, K, epi):
+    """Launches whose tiles fit the chip once or in even rounds: against
+    float64, and bit for bit the rows of a launch with thousands of tiles."""
+    torch = torch_cuda
+    print(f"[gemm bf16 medium] M={M} N={N} K={K} epi={epi}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    A, W, bias = rnd(M, K).bfloat16(), (0.05 * rnd(N, K)).bfloat16(), 0.1 * rnd(N)
+    fp32 = epi in ("resid", "f32")
+    x0 = rnd(M, N)
+
+    def run(times):
+        rows = torch.randperm(M * times, generator=g, device="cuda").int() if fp32 else None
+        out = x0.repeat(times, 1).to(torch.float32 if fp32 else torch.bfloat16)
+        if fp32:
+            out[rows.long()] = out.clone()  # the row of A's row r is rows[r]
+        _kern().gemm(A.repeat(times, 1), W, bias, epi, out, rows)
+        return out[rows.long()] if fp32 else out
+
+    got = run(1)
+    ref = A.double() @ W.double().t() + bias.double()
+    bound = A.double().abs() @ W.double().abs().t()
+    if fp32:
+        want = ref + (x0.double() if epi == "resid" else 0.0)
+        tol = 1e-5 * (bound + x0.double().abs()) + 1e-6
+    else:
+        want = ref * 0.5 * (1 + torch.erf(ref / 2 ** 0.5)) if epi == "gelu" else ref
+        tol = 2.0 ** -8 * want.abs() + 1e-5 * bound + 1e-6
+    assert ((got.double() - want).abs() <= tol).all()
+    times = 2100 * 128 * 128 // (M * N) + 1  # beyond the medium launches
+    assert torch.equal(run(times).view(times, M, N), got.expand(times, M, N))
+
+
 @pytest.mark.parametrize("M,N,K", [(6000, 1536, 384), (20000, 1536, 384), (12000, 768, 192),
                                    (6000, 3072, 768)])
 def test_gemm_gelu_fc1_shapes(torch_cuda, M, N, K):
@@ -692,5 +733,6 @@ def test_workspace_entries_refuse_capture(torch_cuda):
     torch.cuda.synchronize()
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):
+        size.add_(0)
         with pytest.raises(FusionError):
             _kern().attention(qkv, size, [0, 4], 1)
