@@ -145,7 +145,11 @@ template hipError_t launch_layernorm<bf16_t>(const float*, const int*, const flo
 // normalises the pooled row.  The pool reads the state before the block's
 // merge: size-weighted merging keeps sum_t s_t x_t and sum_t s_t, so the
 // pooled vector is the same before and after it.
+// Bound by load latency (one workgroup per sample, 49 rows a wave at 197
+// tokens): POOL_U rows of a wave are in flight together (one at a time took
+// 37 us for 64 samples of 197 tokens, now 21).
 constexpr int POOL_MAXV = 3;  // 16-byte pieces per lane (d <= 768)
+constexpr int POOL_U = 8;
 template <typename T>
 __global__ __launch_bounds__(256) void pool_ln_kernel(
     const float* __restrict__ x, const int* __restrict__ rmap, const float* __restrict__ size,
@@ -163,21 +167,31 @@ __global__ __launch_bounds__(256) void pool_ln_kernel(
 #pragma unroll
   for (int k = 0; k < POOL_MAXV; k++) acc[k] = make_float4(0.f, 0.f, 0.f, 0.f);
   float den = 0.f;
-  for (int t = 1 + wave; t < Tn; t += 4) {
-    const float st = size[base + t];
-    const float4* xr = (const float4*)(x + (size_t)rmap[base + t] * d);
+  for (int t0 = 1 + wave; t0 < Tn; t0 += 4 * POOL_U) {
+    float4 v[POOL_U][POOL_MAXV];
+    float st[POOL_U];
 #pragma unroll
-    for (int k = 0; k < POOL_MAXV; k++) {
-      const int q = lane + 64 * k;
-      if (q < n4) {
-        const float4 v = xr[q];
-        acc[k].x = fmaf(st, v.x, acc[k].x);
-        acc[k].y = fmaf(st, v.y, acc[k].y);
-        acc[k].z = fmaf(st, v.z, acc[k].z);
-        acc[k].w = fmaf(st, v.w, acc[k].w);
-      }
+    for (int u = 0; u < POOL_U; u++) {
+      const int t = base + min(t0 + 4 * u, Tn - 1);
+      st[u] = size[t];
+      const float4* xr = (const float4*)(x + (size_t)rmap[t] * d);
+#pragma unroll
+      for (int k = 0; k < POOL_MAXV; k++)
+        if (64 * k < n4) v[u][k] = xr[min(lane + 64 * k, n4 - 1)];
     }
-    den += st;
+#pragma unroll
+    for (int u = 0; u < POOL_U; u++) {
+      if (t0 + 4 * u >= Tn) break;
+#pragma unroll
+      for (int k = 0; k < POOL_MAXV; k++)
+        if (64 * k < n4) {
+          acc[k].x = fmaf(st[u], v[u][k].x, acc[k].x);
+          acc[k].y = fmaf(st[u], v[u][k].y, acc[k].y);
+          acc[k].z = fmaf(st[u], v[u][k].z, acc[k].z);
+          acc[k].w = fmaf(st[u], v[u][k].w, acc[k].w);
+        }
+      den += st[u];
+    }
   }
 #pragma unroll
   for (int k = 0; k < POOL_MAXV; k++) {
