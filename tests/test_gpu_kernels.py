@@ -305,6 +305,23 @@ def test_attention_ragged(torch_cuda, lengths, H, dh, prec, prop):
 
 
 
+@pytest.mark.parametrize("T", [1, 128, 129, 144, 256, 257, 400, 592])
+def test_attention_split_queries(torch_cuda, T):
+    """One sample, whose query tiles are split over workgroups, gives the bits
+    that it gives inside a batch that fills the chip (CLS rows included)."""
+    torch = torch_cuda
+    print(f"[attention split] T={T}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T)
+    H, n = 3, 180
+    qkv = torch.randn(T, 3 * 64 * H, generator=g, device="cuda").bfloat16()
+    size = torch.randint(1, 4, (T,), generator=g, device="cuda").float()
+    one, cls1 = _kern().attention(qkv, size, [0, T], H, True, T)
+    many, cls = _kern().attention(qkv.repeat(n, 1), size.repeat(n), [T * i for i in range(n + 1)],
+                                  H, True, T)
+    assert torch.equal(many.view(n, T, -1), one.expand(n, T, -1))
+    assert torch.equal(cls, cls1.expand(n, H, T))
+
+
 @pytest.mark.parametrize("lengths,H,dh", [
     ([64, 65, 1, 16, 17, 128], 2, 64),    # chunk and query-block edges
     ([256, 255, 63, 193], 3, 20),         # head padded from 20 to 32 dims
