@@ -148,7 +148,8 @@ __global__ __launch_bounds__(256) void gemm_valu(const T* __restrict__ A,
 // element q of lane l is C[8*(q/4) + 4*(l/32) + q%4][l%32].
 constexpr int NB = 128;
 constexpr int NXCD = 8;
-constexpr long F32_TILES64 = 512;
+// 64-row tiles from which an fp32 launch takes them
+constexpr long F32_TILES64 = 1188;
 // 32 x 32 blocks up to which a bf16 launch takes the small-launch kernel
 constexpr long SMALL_TILES = 2048;
 
@@ -915,27 +916,28 @@ void launch_mid(int bi, const bf16_t* A, int lda, const bf16_t* W, int N, int K,
 
 // ------------------------------------------------------------ fp32 MFMA --
 // MB x MB output tile per workgroup, 4 waves in a 2 x 2 grid, each wave
-// (MB / 32)^2 blocks of v_mfma_f32_16x16x4_f32.  K is consumed 16 floats at a
-// time (64-byte rows, the bf16 kernel's staged layout and chunk permutation)
-// through a ring of NSTG stages filled by the asynchronous global -> LDS path.
-// A lane's 16-byte piece of a staged row feeds four MFMA steps: slot g = l /
-// 16 of step i is k = 16 kt + 4 g + i, in this order for every tile size, so
-// a row's result does not depend on the tile.  Large products are bound by
-// the fp32 matrix rate (50432 x 1536 x 384 with 64-row tiles: 500 us, 119 of
-// the nominal 157 TFLOP/s; 128-row tiles measured 508 us and lost more below
-// that), small ones by the latency of the first stages (1573 x 1152 x 384:
-// 21 us against 62 us for the general kernel).  The product is transposed (W
-// as the row operand): lane (g, c) holds row m = .. + c, columns n = .. + 4 g
-// + q.
-template <int MB, int NSTG>
+// (MB / 32)^2 blocks of v_mfma_f32_16x16x4_f32.  K is consumed KS floats at a
+// time through a ring of NSTG stages filled by the asynchronous global -> LDS
+// path: 32 (128-byte rows, their eight chunks XOR-permuted by row % 8) or,
+// where K is not a multiple of it, 16 (64-byte rows, the bf16 kernel's staged
+// layout).  A lane's 16-byte piece of a staged row feeds four MFMA steps: slot
+// g = l / 16 of step i is k = 16 kt + 4 g + i, in this order for every tile
+// size and KS, so a row's result does not depend on the tile.  Large products
+// are bound by the fp32 matrix rate (nominal 157 TFLOP/s), small ones by the
+// latency of the first stages and the barriers of the K steps (1573 x 1152 x
+// 384: 62 us for the general kernel, 20 for this one).  The product is
+// transposed (W as the row operand): lane (g, c) holds row m = .. + c, columns
+// n = .. + 4 g + q.
+template <int MB, int NSTG, int KS>
 __global__ __launch_bounds__(256) void gemm_mfma_f32(const float* __restrict__ A, int lda,
                                                      const float* __restrict__ W, int N, int K,
                                                      const int* M_dev, int M_host, int n_mt,
                                                      int vec, Epi e) {
-  constexpr int ROWB = 64, KS = 16;
+  constexpr int ROWB = KS * 4, CPR = KS / 4, RPI = 64 / CPR;  // bytes, chunks per row; rows per DMA
   constexpr int WB = MB / 2, NW = WB / 16;       // wave tile rows, 16-row blocks
   constexpr int STGB = 2 * MB * ROWB;            // bytes per stage: A rows, W rows
-  constexpr int DPW = 2 * MB / 16 / 4;           // DMA instructions per wave and stage
+  constexpr int DPW = 2 * MB / RPI / 4;          // DMA instructions per wave and stage
+  static_assert(KS == 16 || KS == 32, "64- or 128-byte rows");
   const int M = M_dev ? *M_dev : M_host;
   const int n_nt = (N + MB - 1) / MB;
   const int id = blockIdx.x;
@@ -948,17 +950,19 @@ __global__ __launch_bounds__(256) void gemm_mfma_f32(const float* __restrict__ A
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int wm = wave >> 1, wn = wave & 1, g = lane >> 4, c = lane & 15;
 
+  // 16-byte chunk c of staged row r
+  auto slot = [](int r, int c) { return KS == 16 ? kslot(r, c) : c ^ (r & 7); };
   const float* sbase[DPW];
   unsigned voff[DPW], dst[DPW];
 #pragma unroll
   for (int u = 0; u < DPW; u++) {
-    const int q = wave * DPW + u;  // 16-row block: A rows first, then W rows
-    const bool isA = q < MB / 16;
-    const int r = (isA ? q : q - MB / 16) * 16 + lane / 4;
+    const int q = wave * DPW + u;  // block of RPI rows: A rows first, then W rows
+    const bool isA = q < MB / RPI;
+    const int r = (isA ? q : q - MB / RPI) * RPI + lane / CPR;
     const int gr = isA ? min(m0 + r, M - 1) : min(n0 + r, N - 1);
     sbase[u] = isA ? A : W;
-    voff[u] = (unsigned)(((size_t)gr * (isA ? lda : K) + kslot(r, lane % 4) * 4) * 4);
-    dst[u] = q * 16 * ROWB;
+    voff[u] = (unsigned)(((size_t)gr * (isA ? lda : K) + slot(r, lane % CPR) * 4) * 4);
+    dst[u] = q * RPI * ROWB;
   }
   const int nk = K / KS;
 #pragma unroll
@@ -986,20 +990,24 @@ __global__ __launch_bounds__(256) void gemm_mfma_f32(const float* __restrict__ A
     }
     const char* Ab = smem + st * STGB;
     const char* Bb = Ab + MB * ROWB;
-    f32x4_t av[NW], bv[NW];
+    f32x4_t av[KS / 16][NW], bv[KS / 16][NW];
 #pragma unroll
-    for (int i = 0; i < NW; i++) {
-      const int ra = wm * WB + i * 16 + c, rb = wn * WB + i * 16 + c;
-      av[i] = *(const f32x4_t*)(Ab + ra * ROWB + (kslot(ra, g) << 4));
-      bv[i] = *(const f32x4_t*)(Bb + rb * ROWB + (kslot(rb, g) << 4));
-    }
+    for (int h = 0; h < KS / 16; h++)
 #pragma unroll
-    for (int q = 0; q < 4; q++)
+      for (int i = 0; i < NW; i++) {
+        const int ra = wm * WB + i * 16 + c, rb = wn * WB + i * 16 + c;
+        av[h][i] = *(const f32x4_t*)(Ab + ra * ROWB + (slot(ra, 4 * h + g) << 4));
+        bv[h][i] = *(const f32x4_t*)(Bb + rb * ROWB + (slot(rb, 4 * h + g) << 4));
+      }
 #pragma unroll
-      for (int i = 0; i < NW; i++)
+    for (int h = 0; h < KS / 16; h++)
 #pragma unroll
-        for (int j = 0; j < NW; j++)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bv[j][q], av[i][q], acc[i][j], 0, 0, 0);
+      for (int q = 0; q < 4; q++)
+#pragma unroll
+        for (int i = 0; i < NW; i++)
+#pragma unroll
+          for (int j = 0; j < NW; j++)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bv[h][j][q], av[h][i][q], acc[i][j], 0, 0, 0);
     st = st + 1 == NSTG ? 0 : st + 1;
     sn = sn + 1 == NSTG ? 0 : sn + 1;
   }
@@ -1058,16 +1066,30 @@ hipError_t launch_gemm<float>(const float* A, int lda, const float* W, int N,
     auto grid = [&](int mb) {
       return ((M_ub + mb - 1) / mb + NXCD - 1) / NXCD * NXCD * ((N + mb - 1) / mb);
     };
-    // 64-row tiles from two of them per CU on (6304 x 384 x 384, 594 tiles:
-    // 25.6 against 26.6 us with 32-row tiles), below that 32-row tiles, whose
-    // K steps wait for less and of which more run at once (1573 x 1152 x 384,
-    // 450 tiles: 21.1 against 24.0 us; 197 x 384 x 1536: 17.8 against 37.0)
-    if (tiles(64) >= F32_TILES64)
-      gemm_mfma_f32<64, 6><<<grid(64), 256, 0, s>>>(A, lda, W, N, K, M_dev, M_host,
-                                                    (M_ub + 63) / 64, vec, e);
-    else
-      gemm_mfma_f32<32, 8><<<grid(32), 256, 0, s>>>(A, lda, W, N, K, M_dev, M_host,
-                                                    (M_ub + 31) / 32, vec, e);
+    // K steps of 32 (whole 128-byte lines) where K has them: 64-row tiles in
+    // two stages from F32_TILES64 of them on, below that 32-row tiles in three,
+    // which wait for less and of which more run at once (us, K steps of 16 /
+    // 32-row / 64-row tiles: 1573 x 1152 x 384 23.3 / 20.1 / 23.4; 3152 x 1536
+    // x 384, 1200 tiles, 48.2 / 43.5 / 45.1; 6304 x 1152 x 384, 1782 tiles,
+    // 63.5 / 63.2 / 57.4; 6304 x 768 x 3072, 1188 tiles, 298 / 287 / 252)
+    auto go = [&](auto mb_c, auto st_c, auto ks_c) {
+      constexpr int MB = decltype(mb_c)::value;
+      gemm_mfma_f32<MB, decltype(st_c)::value, decltype(ks_c)::value><<<grid(MB), 256, 0, s>>>(
+          A, lda, W, N, K, M_dev, M_host, (M_ub + MB - 1) / MB, vec, e);
+    };
+    typedef std::integral_constant<int, 16> I16;
+    typedef std::integral_constant<int, 32> I32;
+    typedef std::integral_constant<int, 64> I64;
+    if (K % 32 == 0) {
+      if (tiles(64) >= F32_TILES64)
+        go(I64{}, std::integral_constant<int, 2>{}, I32{});
+      else
+        go(I32{}, std::integral_constant<int, 3>{}, I32{});
+    } else if (tiles(64) >= 512) {
+      go(I64{}, std::integral_constant<int, 6>{}, I16{});
+    } else {
+      go(I32{}, std::integral_constant<int, 8>{}, I16{});
+    }
     return hipGetLastError();
   }
   dim3 grid((M_ub + 63) / 64, (N + 63) / 64);
