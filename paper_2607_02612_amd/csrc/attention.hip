@@ -598,8 +598,8 @@ __global__ __launch_bounds__(RES_NT, MAXT <= 16 ? 4 : 1) void attention_mfma_res
 // the V reads over all banks.  Heads narrower than 16 NU are padded with
 // zeros.  MAXC chunks of 64 keys, NU groups of 16 dims.  A call on 8 samples
 // of up to 197 tokens with 6 heads of 64 took 2.24 ms with the general kernel
-// (one dot product per lane and key) and takes 58 us with this one, most of
-// it outside the kernel.
+// (one dot product per lane and key) and takes 26.5 us with this one, 25 of
+// them in the kernel.
 template <int MAXC, int NU>
 __global__ __launch_bounds__(256) void attention_mfma_f32(AttnArgs a) {
   const int i = blockIdx.x, h = blockIdx.y, qb = blockIdx.z;
