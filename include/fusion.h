@@ -319,8 +319,8 @@ FUSION_API int fusion_test_merge(const fusion_ragged* in, const int32_t* r, int 
  * a call needs 12 bytes per row plus 16 per sample (each part rounded up to
  * 256 bytes), so batch 256 at 197 tokens takes about 0.6 MiB.  The call
  * makes no allocation and does not synchronise: it is asynchronous on the
- * stream like fusion_run (the host offsets and counts are copied in before
- * it returns).  Every call on one GPU shares that GPU's array: calls that
+ * stream like fusion_run (the host offsets and counts are read before it
+ * returns; a captured call replays with those it was captured with).  Every call on one GPU shares that GPU's array: calls that
  * overlap (other streams, other threads) race, so serialise them.  Errors:
  * FUSION_E_CAPACITY when the call needs more scratch than the array holds,
  * otherwise as fusion_test_merge. */
@@ -358,8 +358,7 @@ FUSION_API int fusion_test_topk_compact(const fusion_ragged* in, const float* sc
  * ws_bytes >= fusion_test_workspace_bytes(batch, rows) bytes, 256-byte
  * aligned, any contents, not used by anything else until the call has
  * finished on its stream; overlapping calls take a buffer each.  The host
- * arrays are read before the call returns (past 895 samples, or 447 with
- * merge counts, it waits for the stream).  Every entry of the outputs is
+ * arrays are read before the call returns.  Every entry of the outputs is
  * written: what the descriptions above leave untouched becomes -1 (packed
  * rows, sizes, ids, offsets and samples past the survivors; merge_dst;
  * cls_scores past a sample's rows; exit_block of continuing samples), -7

@@ -138,9 +138,7 @@ int check_packed_out(const fusion_packed_out* o) {
 
 // The caller's workspace of a _ws entry: large enough, 256-byte aligned, and
 // not under graph capture (the offsets and counts are those of the call).
-// `wait` is set for batches whose host arrays are copied rather than passed as
-// a kernel argument: the call then waits until they are read.
-int check_ws(const void* ws, size_t bytes, size_t need, int ints, hipStream_t s, bool* wait) {
+int check_ws(const void* ws, size_t bytes, size_t need, hipStream_t s) {
   if (!ws || (uintptr_t)ws % 256) return bad("workspace is null or not 256-byte aligned");
   if (bytes < need)
     return api_fail(FUSION_E_CAPACITY, ("the call needs " + std::to_string(need) +
@@ -149,7 +147,6 @@ int check_ws(const void* ws, size_t bytes, size_t need, int ints, hipStream_t s,
   HIP_TRY(hipStreamIsCapturing(s, &st));
   if (st != hipStreamCaptureStatusNone)
     return api_fail(FUSION_E_HIP, "not available while the stream is being captured");
-  *wait = ints > STEP_HOST_INTS;
   return FUSION_OK;
 }
 
@@ -378,16 +375,12 @@ FUSION_API int fusion_test_attention_ws(int precision, const void* qkv, const fl
                                         void* ws, size_t ws_bytes, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   int M = 0, T_ub = 0;
-  bool wait = false;
   if (int rc = check_attention(precision, qkv, size, cu, batch, heads, d, prop_attn, out,
                                cls_scores, tmax, &M, &T_ub))
     return rc;
-  if (int rc = check_ws(ws, ws_bytes, step_scratch_bytes(batch, M), batch + 1, s, &wait)) return rc;
-  if (int rc = attention_impl(precision, qkv, size, cu, batch, heads, d, prop_attn, out,
-                              cls_scores, tmax, M, T_ub, (char*)ws, true, s))
-    return rc;
-  if (wait) HIP_TRY(hipStreamSynchronize(s));
-  return FUSION_OK;
+  if (int rc = check_ws(ws, ws_bytes, step_scratch_bytes(batch, M), s)) return rc;
+  return attention_impl(precision, qkv, size, cu, batch, heads, d, prop_attn, out, cls_scores,
+                        tmax, M, T_ub, (char*)ws, true, s);
 }
 
 FUSION_API int fusion_test_merge(const fusion_ragged* in, const int32_t* r, int id_stride,
@@ -407,15 +400,9 @@ FUSION_API int fusion_test_merge_ws(const fusion_ragged* in, const int32_t* r, i
                                     size_t ws_bytes, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   int M = 0;
-  bool wait = false;
   if (int rc = merge_impl(in, r, id_stride, merge_dst, out, s, nullptr, 0, &M, true)) return rc;
-  if (int rc = check_ws(ws, ws_bytes, step_scratch_bytes(in->batch, M, true), 2 * in->batch + 1, s,
-                        &wait))
-    return rc;
-  if (int rc = merge_impl(in, r, id_stride, merge_dst, out, s, (char*)ws, ws_bytes, &M, true, true))
-    return rc;
-  if (wait) HIP_TRY(hipStreamSynchronize(s));
-  return FUSION_OK;
+  if (int rc = check_ws(ws, ws_bytes, step_scratch_bytes(in->batch, M, true), s)) return rc;
+  return merge_impl(in, r, id_stride, merge_dst, out, s, (char*)ws, ws_bytes, &M, true, true);
 }
 
 FUSION_API int fusion_test_merge_noalloc(const fusion_ragged* in, const int32_t* r,
@@ -468,19 +455,14 @@ FUSION_API int fusion_test_topk_compact_ws(const fusion_ragged* in, const float*
                                            size_t ws_bytes, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   int M = 0, T_ub = 0;
-  bool wait = false;
   if (int rc = check_topk(in, scores, heads, tmax, prune_w, prune_b, keep_ratio, exit_logits,
                           classes, delta, logits, exit_block, precision, ln_g, ln_b, ln_out, out,
                           &M, &T_ub))
     return rc;
-  if (int rc = check_ws(ws, ws_bytes, step_scratch_bytes(in->batch, M), in->batch + 1, s, &wait))
-    return rc;
-  if (int rc = topk_impl(in, scores, heads, tmax, prune_w, prune_b, keep_ratio, exit_logits,
-                         classes, delta, logits, exit_block, precision, ln_g, ln_b, ln_out, out, M,
-                         T_ub, (char*)ws, true, s))
-    return rc;
-  if (wait) HIP_TRY(hipStreamSynchronize(s));
-  return FUSION_OK;
+  if (int rc = check_ws(ws, ws_bytes, step_scratch_bytes(in->batch, M), s)) return rc;
+  return topk_impl(in, scores, heads, tmax, prune_w, prune_b, keep_ratio, exit_logits, classes,
+                   delta, logits, exit_block, precision, ln_g, ln_b, ln_out, out, M, T_ub, (char*)ws,
+                   true, s);
 }
 
 }  // extern "C"

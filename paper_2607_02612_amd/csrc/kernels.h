@@ -178,8 +178,8 @@ struct StepInit {
   int B, M;
   struct { void* p; size_t n; uint32_t v; } fill[STEP_FILLS];
 };
-// Largest number of offsets and merge counts that travel as an argument of
-// the kernel (all arguments, the hidden ones included, stay under 4 KiB).
+// Offsets and merge counts that travel as arguments of one launch (all
+// arguments, the hidden ones included, stay under 4 KiB).
 constexpr int STEP_HOST_INTS = 896;
 hipError_t launch_step_init(const StepInit& a, const int32_t* cu_host, const int32_t* r_host,
                             hipStream_t s);

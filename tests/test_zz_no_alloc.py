@@ -60,3 +60,54 @@ def test_merge_noalloc_capacity_error():
         kernels.merge(x, torch.ones(M, device="cuda"), torch.zeros(M, dtype=torch.int32, device="cuda"),
                       cu, np.zeros(len(lengths), np.int32), 197, noalloc=True)
     assert ei.value.code == -3
+
+
+@pytest.mark.parametrize("B", [447, 448, 895, 896, 2688, 2689, 6000])
+def test_noalloc_reads_its_host_arrays_before_it_returns(B):
+    """Offsets and counts overwritten right after the call, and a captured
+    call replayed after they are gone, on both sides of what one launch
+    carries: equal to the samples merged a few at a time."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2607_02612_amd import kernels
+    print(f"[noalloc host arrays] samples={B}", flush=True)
+    rng = np.random.default_rng(B)
+    lengths = [int(v) for v in rng.integers(1, 12, size=B)]
+    lengths[B // 2] = 640  # the longest sample
+    x, size, origin, cu, r = _case(rng, lengths, 64)
+    T_ = lambda a: torch.from_numpy(a.copy()).cuda()
+    x0, ds, do = T_(x), T_(size), T_(origin)
+    want, dst, rows = x0.clone(), [], []
+    for i in range(0, B, 50):
+        j = min(B, i + 50)
+        p, q = int(cu[i]), int(cu[j])
+        part = want[p:q].clone()
+        o, md = kernels.merge(part, ds[p:q].clone(), do[p:q].clone(), cu[i:j + 1] - cu[i], r[i:j], 640)
+        want[p:q] = part
+        n = int(o["counts"][1])
+        rows.append(o["rows"][:n] + p)
+        dst.append(md)
+    rows, dst = torch.cat(rows), torch.cat(dst)
+
+    def check(xg, o, md):
+        torch.cuda.synchronize()
+        assert torch.equal(xg, want) and torch.equal(md, dst)
+        assert torch.equal(o["rows"][:len(rows)], rows) and bool((o["rows"][len(rows):] == -1).all())
+
+    xb, cb, rb = x0.clone(), cu.copy(), r.copy()
+    o, md = kernels.merge(xb, ds, do, cb, rb, 640, noalloc=True)
+    cb[:], rb[:] = 0, 0
+    check(xb, o, md)
+    cb, rb = cu.copy(), r.copy()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        o, md = kernels.merge(xb, ds, do, cb, rb, 640, noalloc=True)
+    cb[:], rb[:] = 0, 0
+    del cb, rb
+    for k in range(3):
+        xb.copy_(x0)
+        for t in (*o.values(), md):
+            t.fill_(-5)
+        g.replay()
+        check(xb, o, md)
