@@ -697,14 +697,15 @@ __global__ __launch_bounds__(256) void attention_mfma_f32(AttnArgs a) {
 #pragma unroll
   for (int ch = 0; ch < MAXC; ch++) {
     if (ch * AKC >= Tn || !act) continue;
+    float lt[4];
 #pragma unroll
-    for (int tt = 0; tt < 4; tt++)
+    for (int tt = 0; tt < 4; tt++) {
+      f32x4_t& e = S[4 * ch + tt];
 #pragma unroll
-      for (int j = 0; j < 4; j++) {
-        const float e = expf(S[4 * ch + tt][j] - mx);
-        S[4 * ch + tt][j] = e;
-        l += e;
-      }
+      for (int j = 0; j < 4; j++) e[j] = expf(e[j] - mx);
+      lt[tt] = (e[0] + e[1]) + (e[2] + e[3]);
+    }
+    l += (lt[0] + lt[1]) + (lt[2] + lt[3]);
   }
   l = sum_xor32(sum_xor16(l));
   if (a.cls_scores && q0 == 0 && c == 0) {
