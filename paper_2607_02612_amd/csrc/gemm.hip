@@ -106,7 +106,8 @@ __global__ __launch_bounds__(256) void gemm_valu(const T* __restrict__ A,
 // ------------------------------------------------------------ bf16 MFMA --
 // MBx128 output tile per workgroup (MB = 256: 8 waves in a 4x2 grid; 128: 4
 // waves, 2x2; 64: 2 waves side by side), each wave a 64x64 sub-tile of 2x2
-// v_mfma_f32_32x32x16_bf16 blocks.
+// v_mfma_f32_32x32x16_bf16 blocks; launches with few 64-row tiles split
+// each into 4 waves of 32x64 (1x2 blocks) instead, which changes no result.
 //
 // K is consumed in steps of KSV = 32 through a ring of three LDS stages
 // (64-wide steps with two stages measured slower on every shape, long K
@@ -148,6 +149,8 @@ __global__ __launch_bounds__(256) void gemm_valu(const T* __restrict__ A,
 // element q of lane l is C[8*(q/4) + 4*(l/32) + q%4][l%32].
 constexpr int NB = 128;
 constexpr int NXCD = 8;
+// 64-row tiles below which a bf16 launch splits them over 32-row waves
+constexpr long THIN_TILES = 768;
 // 64-row tiles from which an fp32 launch takes them
 constexpr long F32_TILES64 = 1188;
 // 32 x 32 blocks up to which a bf16 launch takes the small-launch kernel
@@ -175,13 +178,13 @@ __device__ __forceinline__ void wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
 }
 
-// MB = 256, 128 or 64 rows per tile; each wave owns 64 rows x 64 columns (2 x
-// 2 MFMA blocks), the waves in a grid of MB / 64 rows x 2 columns.  Every
-// layout accumulates each output element over the same 16-wide K pieces in
-// the same order from the same bias start, so the results do not depend on
-// MB.  KSV = K step (32).
-template <int EPI, int MB, int KSV>
-__global__ __launch_bounds__(MB * 2, MB == 128 ? 3 : 1) void gemm_mfma_bf16(
+// MB = 256, 128 or 64 rows per tile; each wave owns WR * 32 rows x 64
+// columns (WR = 2: 2 x 2 MFMA blocks, WR = 1: 1 x 2), the waves in a grid of
+// MB / (32 WR) rows x 2 columns.  Every layout accumulates each output
+// element over the same 16-wide K pieces in the same order from the same
+// bias start, so the results do not depend on MB or WR.  KSV = K step (32).
+template <int EPI, int MB, int KSV, int WR>
+__global__ __launch_bounds__(MB / (32 * WR) * 128, MB == 128 ? 3 : 1) void gemm_mfma_bf16(
     const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W,
     int N, int K, const int* M_dev, int M_host, int n_mt, Epi e) {
   static_assert(KSV == 32, "K step of 32");
@@ -189,7 +192,8 @@ __global__ __launch_bounds__(MB * 2, MB == 128 ? 3 : 1) void gemm_mfma_bf16(
   constexpr int ROWB = KS * 2;                        // bytes per staged row
   constexpr int CPR = KS / 8;                         // 16-byte chunks per staged row
   constexpr int RPI = 64 / CPR;                       // rows per DMA instruction
-  constexpr int WR = 2, WMR = 32 * WR;                // 32-row blocks and rows per wave
+  static_assert(WR == 1 || WR == 2, "32 or 64 rows per wave");
+  constexpr int WMR = 32 * WR;                        // rows per wave
   constexpr int NWV = MB / WMR * 2;                   // waves
   constexpr int NT = NWV * 64;                        // threads
   constexpr int STGB = (MB + NB) * ROWB;              // bytes per stage
@@ -1155,13 +1159,20 @@ hipError_t launch_gemm<bf16_t>(const bf16_t* A, int lda, const bf16_t* W,
   const int mb = small ? 64 : big ? 256 : 128;
   const int n_mt = (M_ub + mb - 1) / mb;
   const int grid = (n_mt + NXCD - 1) / NXCD * NXCD * n_nt;
+  // 32-row waves (twice the waves per tile) for 64-row tiles when the launch
+  // has fewer tiles than the CUs hold at once (us, 64- / 32-row waves: 197 x
+  // 1152 x 96 4.2 / 3.5, with residual 6.0 / 4.9; 3000 x 768 x 352 8.1 / 7.4;
+  // from K about 1000 on they are even)
+  const bool thin = small && (long)((Mx + 63) / 64) * n_nt < THIN_TILES;
 #define FUSION_GEMM_LAUNCH(E)                                                                    \
-  if (small)                                                                               \
-    gemm_mfma_bf16<E, 64, 32><<<grid, 128, 0, s>>>(A, lda, W, N, K, M_dev, M_host, n_mt, e); \
+  if (thin)                                                                                     \
+    gemm_mfma_bf16<E, 64, 32, 1><<<grid, 256, 0, s>>>(A, lda, W, N, K, M_dev, M_host, n_mt, e); \
+  else if (small)                                                                               \
+    gemm_mfma_bf16<E, 64, 32, 2><<<grid, 128, 0, s>>>(A, lda, W, N, K, M_dev, M_host, n_mt, e); \
   else if (big)                                                                                 \
-    gemm_mfma_bf16<E, 256, 32><<<grid, 512, 0, s>>>(A, lda, W, N, K, M_dev, M_host, n_mt, e); \
+    gemm_mfma_bf16<E, 256, 32, 2><<<grid, 512, 0, s>>>(A, lda, W, N, K, M_dev, M_host, n_mt, e); \
   else                                                                                          \
-    gemm_mfma_bf16<E, 128, 32><<<grid, 256, 0, s>>>(A, lda, W, N, K, M_dev, M_host, n_mt, e)
+    gemm_mfma_bf16<E, 128, 32, 2><<<grid, 256, 0, s>>>(A, lda, W, N, K, M_dev, M_host, n_mt, e)
   switch (e.mode) {
     case EPI_STORE: FUSION_GEMM_LAUNCH(EPI_STORE); break;
     case EPI_GELU: FUSION_GEMM_LAUNCH(EPI_GELU); break;

@@ -140,7 +140,9 @@ def test_gemm_bf16_small_launches(torch_cuda, M, N, K, epi):
     (4225, 1000, 64, "store"), (4300, 1004, 192, "f32"), (9000, 520, 128, "gelu"),
     (12608, 384, 1536, "resid"),                                    # 128-row tiles, two stages
     (12300, 1000, 64, "gelu"), (33000, 384, 128, "resid"), (25000, 1000, 64, "store"),  # more rounds
-    (300, 384, 96, "resid"), (2500, 1000, 32, "store"),             # K not a multiple of 64
+    (300, 384, 96, "resid"), (2500, 1000, 32, "store"),             # K not a multiple of 64:
+    (1, 64, 32, "store"), (65, 1004, 160, "f32"), (1573, 520, 96, "gelu"),  # 32-row waves
+    (4097, 1500, 96, "resid"),                                      # 64-row waves
 ])
 def test_gemm_bf16_medium_launches(torch_cuda, M, N, K, epi):
     """Launches whose tiles fit the chip once or in even rounds: against
