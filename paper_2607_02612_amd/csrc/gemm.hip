@@ -110,8 +110,8 @@ __global__ __launch_bounds__(256) void gemm_valu(const T* __restrict__ A,
 // each into 4 waves of 32x64 (1x2 blocks) instead, which changes no result.
 //
 // K is consumed in steps of KSV = 32 through a ring of three LDS stages
-// (64-wide steps with two stages measured slower on every shape, long K
-// included).  A and W tiles reach LDS through the gfx950 asynchronous
+// (64-wide steps with two stages measured slower in these workgroups of 4
+// waves on every shape, long K included).  A and W tiles reach LDS through the gfx950 asynchronous
 // global->LDS path (global_load_lds_dwordx4): each wave-wide instruction
 // writes 64 lanes x 16 bytes contiguously, i.e. 16 rows of 64 bytes,
 // without passing through VGPRs, so later K steps are in
@@ -1150,12 +1150,14 @@ hipError_t launch_gemm<bf16_t>(const bf16_t* A, int lda, const bf16_t* W,
   // several times over, 64 when 128-row tiles would leave CUs idle (only K
   // that the medium kernel does not take)
   const bool small = t128 < 512;
-  // K steps of 32 with three stages everywhere: 64-wide steps (two stages,
-  // half the barriers) measured slower on every shape here, long K included
-  // (not for the GELU epilogue, whose vector work overlaps better with
-  // three 4-wave workgroups per CU than with two 8-wave ones)
+  // (256 rows not for the GELU epilogue, whose vector work overlaps better with
+  // three 4-wave workgroups per CU than with two 8-wave ones; the limit is four
+  // tiles a CU: below it the direct residual epilogue of 256-row tiles costs 15
+  // to 33 %, 39500 x 768 x 768 103 us in 128-row tiles / 124 in 256-row ones,
+  // 87000 x 384 x 384 80 / 106, and the plain store is even, 13800 x 2304 x 768
+  // 75 / 71, 26400 x 1152 x 384 43.3 / 45.3)
   const bool big = e.mode != EPI_GELU &&
-                   (long)((Mx + 255) / 256) * n_nt >= 925;
+                   (long)((Mx + 255) / 256) * n_nt >= 1024;
   const int mb = small ? 64 : big ? 256 : 128;
   const int n_mt = (M_ub + mb - 1) / mb;
   const int grid = (n_mt + NXCD - 1) / NXCD * NXCD * n_nt;
