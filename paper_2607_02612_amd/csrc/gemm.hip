@@ -882,29 +882,34 @@ __global__ __launch_bounds__(512, 2) void gemm_mfma_bf16_mid(
   }
 }
 
-// Medium launches by the number of tiles (two workgroups a CU: 512 at a time;
-// the 3-stage kernel above holds 768 of its 128-row tiles), us per launch on
-// cold operands, 3-stage kernel / this one:
+// Medium launches by the tiles of the XCD that gets the most row panels (all
+// column tiles of a panel run on one XCD, whose 32 CUs hold 64 of these
+// workgroups at a time; of the 3-stage kernel's 128-row ones 96).  82 panels of
+// 6 tiles are 492 in all, but 66 on two XCDs: 10431 x 768 x 768 took 39.0 us as
+// "fits once" and takes 35 in the 3-stage kernel; 5200 x 768 x 192 + GELU, 66
+// 64-row tiles there, 9.4 and 8.4 in 128-row ones.  us per launch on cold
+// operands, 3-stage kernel / this one:
 //   64-row tiles fit once: BI = 1 (384 x 1536 with residual: 2400 rows 18.5 /
 //     13.4, 9000 rows 24.8 / 20.4; 1536 x 384 with GELU: 2400 rows 10.1 / 8.5)
 //   128-row tiles fit once: BI = 2 (384 x 1536: 12608 rows 35.9 / 26.2, 20000
 //     rows 46.9 / 33.1; 768 x 3072: 9456 rows 85.9 / 52.2; 1152 x 384: 6304
 //     rows 14.8 / 10.8; 1536 x 384: 4700 rows 17.7 / 12.5)
-//   up to 768: the 3-stage kernel, which holds them all (384 x 1536: 28000
+//   up to 96: the 3-stage kernel, which holds them all (384 x 1536: 28000
 //     rows 58.9 / 60.8; 1152 x 384: 9000 rows 15.7 / 16.8)
-//   up to 1024: BI = 2 in two even rounds (384 x 1536: 36928 rows 87.5 / 77.4;
+//   up to 128: BI = 2 in two even rounds (384 x 1536: 36928 rows 87.5 / 77.4;
 //     384 x 384: 40000 rows 41.6 / 37.8), not with GELU, whose vector work
 //     prefers three independent workgroups (1536 x 384 inside a pass: 9500
 //     rows 25.4 / 28.0)
-//   up to 1850, plain store only: BI = 2 (2304 x 768: 12608 rows 66.2 / 57.2;
-//     1152 x 384: 20000 rows 28.8 / 26.3, 26000 rows 38.7 / 37.2, but 30000
-//     rows 43.7 / 46.9 in 256-row tiles)
+//   plain store further, the longer K the further: 768 and up to 240 (2304 x
+//     768: 12608 rows 66.2 / 57.2), 384 to 144 (1152 x 384: 14773 rows 28.2 /
+//     26.7, 17581 31.3 / 32.5, 24898 41.7 / 43.4), below to 112 (576 x 192:
+//     20922 rows 15.2 / 14.7, 24898 17.1 / 17.6)
 //   beyond, the 3-stage kernel (384 x 1536: 50432 rows 109.9 / 108.8)
-// Whole passes: 64 images of the Tab. I model 1369 -> 1299 us.
-int mid_blocks(int mode, long t64, long t128) {
-  if (t64 <= 512) return 1;
-  const long most = mode == EPI_GELU ? 512 : mode == EPI_STORE ? 1850 : 1024;
-  if (t128 <= 512 || (t128 > 768 && t128 <= most)) return 2;
+int mid_blocks(int mode, int K, long x64, long x128) {
+  if (x64 <= 64) return 1;
+  const long most = mode == EPI_GELU ? 64
+                    : mode != EPI_STORE ? 128 : K >= 768 ? 240 : K >= 384 ? 144 : 112;
+  if (x128 <= 64 || (x128 > 96 && x128 <= most)) return 2;
   return 0;
 }
 template <int EPI>
@@ -1133,8 +1138,9 @@ hipError_t launch_gemm<bf16_t>(const bf16_t* A, int lda, const bf16_t* W,
     return hipGetLastError();
   }
   const int n_nt = (N + NB - 1) / NB;
-  const long t128 = (long)((Mx + 127) / 128) * n_nt;
-  const int bi = K % 64 == 0 ? mid_blocks(e.mode, (long)((Mx + 63) / 64) * n_nt, t128) : 0;
+  // tiles of the XCD that gets the most row panels
+  auto per_xcd = [&](int mb) { return (long)((Mx + mb * NXCD - 1) / (mb * NXCD)) * n_nt; };
+  const int bi = K % 64 == 0 ? mid_blocks(e.mode, K, per_xcd(64), per_xcd(128)) : 0;
   if (bi) {
     switch (e.mode) {
       case EPI_STORE: launch_mid<EPI_STORE>(bi, A, lda, W, N, K, M_dev, M_host, M_ub, e, s); break;
@@ -1149,7 +1155,7 @@ hipError_t launch_gemm<bf16_t>(const bf16_t* A, int lda, const bf16_t* W,
   // tile rows: 256 (8 waves) when there are enough tiles to fill the CUs
   // several times over, 64 when 128-row tiles would leave CUs idle (only K
   // that the medium kernel does not take)
-  const bool small = t128 < 512;
+  const bool small = K % 64 != 0 && (long)((Mx + 127) / 128) * n_nt < 512;
   // (256 rows not for the GELU epilogue, whose vector work overlaps better with
   // three 4-wave workgroups per CU than with two 8-wave ones; the limit is four
   // tiles a CU: below it the direct residual epilogue of 256-row tiles costs 15
