@@ -153,8 +153,20 @@ constexpr int NXCD = 8;
 constexpr long THIN_TILES = 768;
 // 64-row tiles from which an fp32 launch takes them
 constexpr long F32_TILES64 = 1188;
-// 32 x 32 blocks up to which a bf16 launch takes the small-launch kernel
+// 32 x 32 blocks up to which a bf16 launch takes the small-launch kernel: it
+// saves the waits of a long K, while the medium kernel, which writes rows
+// through LDS in whole lines, wins the sooner the less there is to wait for
+// (us at the blocks, medium / small kernel: K = 64, 576 columns 432 3.1 / 2.8,
+// 594 3.1 / 3.1, 1530 3.5 / 4.7; K = 192, 576 columns 594 4.2 / 4.5, 384 with
+// residual 600 5.2 / 5.5, but 768 with GELU 576 5.2 / 4.8, 1512 5.4 / 5.6; K =
+// 256, 384 columns 900 5.0 / 4.9, 1524 5.2 / 6.1; K = 768, 2304 columns 2016
+// 11.2 / 9.0).  GELU runs slower on two medium workgroups of a CU than on the
+// small ones (x64, see mid_blocks, above 32: 2713 x 768 x 192 6.6 / 6.1).
 constexpr long SMALL_TILES = 2048;
+inline long small_tiles(int mode, int K, long x64) {
+  if (K > 320 || (mode == EPI_GELU && x64 > 32)) return SMALL_TILES;
+  return K <= (mode == EPI_GELU || mode == EPI_F32 ? 128 : 192) ? 512 : 1024;
+}
 
 // 16-byte chunk c of staged row r (64-byte rows: four chunks)
 __device__ __forceinline__ int kslot(int r, int c) { return c ^ ((r >> 2) & 3); }
@@ -674,8 +686,10 @@ __global__ __launch_bounds__(64 * NWV) void gemm_mfma_bf16_small(
 // K given; large-tile kernel / 1 block / 2 blocks / 4 blocks a workgroup):
 //   up to 256, one per CU: one block and four loading waves
 //     (197, 384 x 1536: 15.2 / 6.9 / 8.2 / 9.5; 197, 1152 x 384: 5.3 / 3.5 / 3.8 / 4.6)
-//   up to 900: two blocks (788, 1152 x 384: 5.6 / 5.0 / 4.7 / 5.1)
-//   up to SMALL_TILES: four blocks, which load each operand row for two
+//   up to 1024, two workgroups per CU: two blocks (788, 1152 x 384: 5.6 / 5.0 /
+//     4.7 / 5.1; 1337, 768 x 3072, 1008 blocks: two 18.7, four 20.2; but 2907,
+//     384 x 1536, 1092 blocks: two 17.4, four 15.5)
+//   up to small_tiles(): four blocks, which load each operand row for two
 //     (1576, 1152 x 384: 6.9 / 8.2 / 7.7 / 6.2; 2400, 768 x 3072: 35.6 / 41 / 37 / 26)
 //   beyond, the 64- and 128-row tiles (2400, 1152 x 384: 7.9 against 8.1)
 template <int EPI>
@@ -684,7 +698,7 @@ void launch_small(const bf16_t* A, int lda, const bf16_t* W, int N, int K, const
   const int m32 = (M_ub + 31) / 32, m64 = (M_ub + 63) / 64, n32 = (N + 31) / 32, n64 = (N + 63) / 64;
   if (t32 <= 256)
     gemm_mfma_bf16_small<EPI, 1, 1, 4, 4><<<m32 * n32, 256, 0, s>>>(A, lda, W, N, K, M_dev, M_host, e);
-  else if (t32 <= 900)
+  else if (t32 <= 1024)
     gemm_mfma_bf16_small<EPI, 1, 2, 4, 4><<<m32 * n64, 256, 0, s>>>(A, lda, W, N, K, M_dev, M_host, e);
   else
     gemm_mfma_bf16_small<EPI, 2, 2, 3, 4><<<m64 * n64, 256, 0, s>>>(A, lda, W, N, K, M_dev, M_host, e);
@@ -1125,8 +1139,11 @@ hipError_t launch_gemm<bf16_t>(const bf16_t* A, int lda, const bf16_t* W,
     return hipErrorInvalidValue;
   if ((e.mode == EPI_STORE || e.mode == EPI_GELU) && (N % 8 != 0 || e.ldo % 8 != 0))
     return hipErrorInvalidValue;
+  const int n_nt = (N + NB - 1) / NB;
+  // tiles of mb rows of the XCD that gets the most row panels
+  auto per_xcd = [&](int mb) { return (long)((Mx + mb * NXCD - 1) / (mb * NXCD)) * n_nt; };
   const long t32 = (long)((Mx + 31) / 32) * ((N + 31) / 32);
-  if (K % 64 == 0 && t32 <= SMALL_TILES) {
+  if (K % 64 == 0 && t32 <= small_tiles(e.mode, K, per_xcd(64))) {
     switch (e.mode) {
       case EPI_STORE: launch_small<EPI_STORE>(A, lda, W, N, K, M_dev, M_host, M_ub, t32, e, s); break;
       case EPI_GELU: launch_small<EPI_GELU>(A, lda, W, N, K, M_dev, M_host, M_ub, t32, e, s); break;
@@ -1137,9 +1154,6 @@ hipError_t launch_gemm<bf16_t>(const bf16_t* A, int lda, const bf16_t* W,
     }
     return hipGetLastError();
   }
-  const int n_nt = (N + NB - 1) / NB;
-  // tiles of the XCD that gets the most row panels
-  auto per_xcd = [&](int mb) { return (long)((Mx + mb * NXCD - 1) / (mb * NXCD)) * n_nt; };
   const int bi = K % 64 == 0 ? mid_blocks(e.mode, K, per_xcd(64), per_xcd(128)) : 0;
   if (bi) {
     switch (e.mode) {

@@ -143,6 +143,8 @@ def test_gemm_bf16_small_launches(torch_cuda, M, N, K, epi):
     (300, 384, 96, "resid"), (2500, 1000, 32, "store"),             # K not a multiple of 64:
     (1, 64, 32, "store"), (65, 1004, 160, "f32"), (1573, 520, 96, "gelu"),  # 32-row waves
     (4097, 1500, 96, "resid"),                                      # 64-row waves
+    (1049, 520, 64, "store"), (1700, 384, 192, "resid"), (3100, 384, 320, "f32"),  # short K
+    (1084, 3072, 64, "gelu"), (10431, 768, 64, "resid"),            # 9 and 11 panels on an XCD
 ])
 def test_gemm_bf16_medium_launches(torch_cuda, M, N, K, epi):
     """Launches whose tiles fit the chip once or in even rounds: against
