@@ -151,8 +151,6 @@ constexpr int NB = 128;
 constexpr int NXCD = 8;
 // 64-row tiles below which a bf16 launch splits them over 32-row waves
 constexpr long THIN_TILES = 768;
-// 64-row tiles from which an fp32 launch takes them
-constexpr long F32_TILES64 = 1188;
 // 32 x 32 blocks up to which a bf16 launch takes the small-launch kernel: it
 // saves the waits of a long K, while the medium kernel, which writes rows
 // through LDS in whole lines, wins the sooner the less there is to wait for
@@ -1089,12 +1087,15 @@ hipError_t launch_gemm<float>(const float* A, int lda, const float* W, int N,
     auto grid = [&](int mb) {
       return ((M_ub + mb - 1) / mb + NXCD - 1) / NXCD * NXCD * ((N + mb - 1) / mb);
     };
-    // K steps of 32 (whole 128-byte lines) where K has them: 64-row tiles in
-    // two stages from F32_TILES64 of them on, below that 32-row tiles in three,
-    // which wait for less and of which more run at once (us, K steps of 16 /
-    // 32-row / 64-row tiles: 1573 x 1152 x 384 23.3 / 20.1 / 23.4; 3152 x 1536
-    // x 384, 1200 tiles, 48.2 / 43.5 / 45.1; 6304 x 1152 x 384, 1782 tiles,
-    // 63.5 / 63.2 / 57.4; 6304 x 768 x 3072, 1188 tiles, 298 / 287 / 252)
+    // K steps of 32 (whole 128-byte lines) where K has them: 32-row tiles in
+    // three stages, of which more run at once and wait for less, or 64-row
+    // tiles in two, which read each operand half as often.  The 64-row ones
+    // win with more than three of them a CU, the sooner the longer K (us,
+    // 32-row / 64-row tiles at the number of 64-row tiles: K = 192, 384
+    // columns 1800 37.3 / 38.5, 1152 columns 2394 43.3 / 42.2; K = 384, 1536
+    // columns 1200 39.8 / 41.7, 2400 74.8 / 69.2; K = 768, 384 columns 1056
+    // 65.4 / 67.1, 1536 columns 1128 68.3 / 63.8; K = 1536, 888 110 / 98;
+    // over 231 shapes the rule loses 0.5 % to the better of the two)
     auto go = [&](auto mb_c, auto st_c, auto ks_c) {
       constexpr int MB = decltype(mb_c)::value;
       gemm_mfma_f32<MB, decltype(st_c)::value, decltype(ks_c)::value><<<grid(MB), 256, 0, s>>>(
@@ -1104,7 +1105,7 @@ hipError_t launch_gemm<float>(const float* A, int lda, const float* W, int N,
     typedef std::integral_constant<int, 32> I32;
     typedef std::integral_constant<int, 64> I64;
     if (K % 32 == 0) {
-      if (tiles(64) >= F32_TILES64)
+      if (tiles(64) >= 768 + (3 << 16) / std::max(K, 192))
         go(I64{}, std::integral_constant<int, 2>{}, I32{});
       else
         go(I32{}, std::integral_constant<int, 3>{}, I32{});

@@ -228,8 +228,10 @@ def test_gemm_fp32(torch_cuda, M, N, K, epi):
     (4200, 516, 80, "resid", 0),   # 64-row tiles with edges
     (33, 36, 32, "store", 0),      # K steps of 32: fewer than, and more than, the stages
     (65, 68, 160, "resid", 0),
-    (4300, 1100, 32, "gelu", 0),   # the same on 64-row tiles
+    (4300, 1100, 32, "gelu", 0),   # the same with more tiles
     (4300, 1090, 96, "f32", 0),
+    (6400, 1150, 96, "f32", 0),    # 64-row tiles: from 1792 of them at K = 96,
+    (4100, 1180, 512, "resid", 0),  # 1152 at K = 512
     (40, 64, 40, "store", 0),      # K not a multiple of 16: general kernel
     (40, 64, 64, "store", 1),      # operands off 16-byte alignment: general kernel
 ])
