@@ -980,9 +980,10 @@ __global__ __launch_bounds__(256) void gemm_mfma_f32(const float* __restrict__ A
     const int q = wave * DPW + u;  // block of RPI rows: A rows first, then W rows
     const bool isA = q < MB / RPI;
     const int r = (isA ? q : q - MB / RPI) * RPI + lane / CPR;
-    const int gr = isA ? min(m0 + r, M - 1) : min(n0 + r, N - 1);
-    sbase[u] = isA ? A : W;
-    voff[u] = (unsigned)(((size_t)gr * (isA ? lda : K) + slot(r, lane % CPR) * 4) * 4);
+    // (from the tile's first row: operands of any size within 32-bit offsets)
+    const int dr = isA ? min(r, M - 1 - m0) : min(r, N - 1 - n0);
+    sbase[u] = isA ? A + (size_t)m0 * lda : W + (size_t)n0 * K;
+    voff[u] = (unsigned)((dr * (isA ? lda : K) + slot(r, lane % CPR) * 4) * 4);
     dst[u] = q * RPI * ROWB;
   }
   const int nk = K / KS;
@@ -1077,10 +1078,12 @@ hipError_t launch_gemm<float>(const float* A, int lda, const float* W, int N,
                               const Epi& e, hipStream_t s) {
   if (M_ub <= 0) return hipSuccess;
   const int Mx = M_est > 0 ? std::min(M_est, M_ub) : M_ub;
-  // matrix cores: whole 16-float K steps, 16-byte aligned operand rows within
-  // 32-bit byte offsets; anything else takes the general kernel
+  // matrix cores: whole 16-float K steps, 16-byte aligned operand rows, a
+  // tile's 64 rows within 32-bit byte offsets (so whether a row takes this
+  // order of sums does not depend on the number of rows); anything else takes
+  // the general kernel
   if (K >= 16 && K % 16 == 0 && lda % 4 == 0 && ((uintptr_t)A | (uintptr_t)W) % 16 == 0 &&
-      (size_t)M_ub * lda * 4 <= 0xFFFFFFFFull && (size_t)N * K * 4 <= 0xFFFFFFFFull) {
+      std::max(lda, K) <= 1 << 22) {
     const int vec = N % 4 == 0 && e.ldo % 4 == 0 &&
                     ((uintptr_t)e.out | (uintptr_t)e.bias | (uintptr_t)e.pos) % 16 == 0;
     auto tiles = [&](int mb) { return (long)((Mx + mb - 1) / mb) * ((N + mb - 1) / mb); };

@@ -268,6 +268,23 @@ def test_gemm_fp32_tiles(torch_cuda, M, N, K, epi, shift):
     assert np.array_equal(one.cpu().numpy()[0], g[rows[M - 1]])
 
 
+def test_gemm_fp32_rows_past_4_gib(torch_cuda):
+    """An operand of more than 4 GiB: rows at its start, on both sides of the
+    limit and at its end have the bits they have in a small product."""
+    torch = torch_cuda
+    M, N, K = (1 << 20) + 4099, 36, 1024
+    print(f"[gemm fp32] M={M} N={N} K={K}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    A = torch.randn(M, K, generator=g, device="cuda")
+    W, bias = torch.randn(N, K, generator=g, device="cuda"), torch.randn(N, generator=g, device="cuda")
+    out = torch.empty(M, N, device="cuda")
+    _kern().gemm(A, W, bias, "store", out)
+    for i in (0, (1 << 20) - 70, M - 130):
+        part = torch.empty(130, N, device="cuda")
+        _kern().gemm(A[i:i + 130], W, bias, "store", part)
+        assert torch.equal(out[i:i + 130], part), i
+
+
 # ------------------------------------------------------------- attention --
 ATT_CASES = [
     # lengths, heads, dh, precision, prop_attn
