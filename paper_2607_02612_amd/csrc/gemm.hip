@@ -912,15 +912,15 @@ __global__ __launch_bounds__(512, 2) void gemm_mfma_bf16_mid(
 //     384 x 384: 40000 rows 41.6 / 37.8), not with GELU, whose vector work
 //     prefers three independent workgroups (1536 x 384 inside a pass: 9500
 //     rows 25.4 / 28.0)
-//   plain store further, the longer K the further: 768 and up to 240 (2304 x
-//     768: 12608 rows 66.2 / 57.2), 384 to 144 (1152 x 384: 14773 rows 28.2 /
-//     26.7, 17581 31.3 / 32.5, 24898 41.7 / 43.4), below to 112 (576 x 192:
-//     20922 rows 15.2 / 14.7, 24898 17.1 / 17.6)
+//   plain store further: K of 384 and more up to 240 (2304 x 768: 12608 rows
+//     66.2 / 57.2; 1152 x 384 inside a pass, operands just written: 19200 rows
+//     29.2 / 27.4, 23500 rows 34.4 / 33.6), below to 112 (576 x 192: 20922 rows
+//     15.2 / 14.7, 24898 17.1 / 17.6, inside a pass 39400 rows 20.8 / 21.7)
 //   beyond, the 3-stage kernel (384 x 1536: 50432 rows 109.9 / 108.8)
 int mid_blocks(int mode, int K, long x64, long x128) {
   if (x64 <= 64) return 1;
   const long most = mode == EPI_GELU ? 64
-                    : mode != EPI_STORE ? 128 : K >= 768 ? 240 : K >= 384 ? 144 : 112;
+                    : mode != EPI_STORE ? 128 : K >= 384 ? 240 : 112;
   if (x128 <= 64 || (x128 > 96 && x128 <= most)) return 2;
   return 0;
 }
@@ -1175,13 +1175,14 @@ hipError_t launch_gemm<bf16_t>(const bf16_t* A, int lda, const bf16_t* W,
   // that the medium kernel does not take)
   const bool small = K % 64 != 0 && (long)((Mx + 127) / 128) * n_nt < 512;
   // (256 rows not for the GELU epilogue, whose vector work overlaps better with
-  // three 4-wave workgroups per CU than with two 8-wave ones; the limit is four
-  // tiles a CU: below it the direct residual epilogue of 256-row tiles costs 15
-  // to 33 %, 39500 x 768 x 768 103 us in 128-row tiles / 124 in 256-row ones,
-  // 87000 x 384 x 384 80 / 106, and the plain store is even, 13800 x 2304 x 768
-  // 75 / 71, 26400 x 1152 x 384 43.3 / 45.3)
+  // three 4-wave workgroups per CU than with two 8-wave ones.  The direct
+  // residual epilogue of 256-row tiles needs four of them a CU: 39500 x 768 x
+  // 768, 930 tiles, takes 103 us in 128-row tiles and 124 in 256-row ones, 87000
+  // x 384 x 384, 1020 tiles, 80 and 106.  The plain store, which both stage
+  // alike, takes them where the medium kernel ends: 26700 x 1152 x 384 inside a
+  // pass, 945 tiles, 36.4 and 34.0, 13800 x 2304 x 768 72.9 and 68.3)
   const bool big = e.mode != EPI_GELU &&
-                   (long)((Mx + 255) / 256) * n_nt >= 1024;
+                   (long)((Mx + 255) / 256) * n_nt >= (e.mode == EPI_STORE ? 925 : 1024);
   const int mb = small ? 64 : big ? 256 : 128;
   const int n_mt = (M_ub + mb - 1) / mb;
   const int grid = (n_mt + NXCD - 1) / NXCD * NXCD * n_nt;

@@ -51,3 +51,39 @@ def test_block1_stage_parity(torch_cuda, name, batch, tol, stage):
         worst = max(worst, err)
         assert err <= tol, (i, err)
     print(f"  max |dx| = {worst:.3e}")
+
+
+@pytest.mark.parametrize("routers,rho,delta", [("closed", 1.5, 1.0), ("open", 1.0, 1.0),
+                                               ("bias", 0.5, 0.1)])
+def test_rows_far_from_those_expected(routers, rho, delta):
+    """The GEMM kernels are chosen for the rows that the routers give at their
+    bias and for all samples live.  Routers that merge nothing or all they may,
+    and samples that leave early, give each image the bits of a run of its own."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    cfg, W, imgs = pu.make("deit_ti", affine="random")
+    B = 40
+    x = torch.from_numpy(imgs[:B]).cuda()
+    B = x.shape[0]
+    if routers != "bias":
+        for b in cfg["merges"]:  # each block's CLS rows point along their mean
+            m = pu.gpu_model(cfg, W, 4)
+            m.set_exit_thresholds([1.0] * len(cfg["exits"]))
+            mu = np.stack([s[0] for s in m.debug_state(x[:4].contiguous(), b, 2)[0]]).mean(0)
+            m.close()
+            W[f"blk{b}.router_w"] = ((-40 if routers == "closed" else 40) * mu
+                                     / np.dot(mu, mu)).astype(np.float32)
+    out = []
+    for n in (B, 1):
+        m = pu.gpu_model(cfg, W, n)
+        m.set_exit_thresholds([delta] * len(cfg["exits"]))
+        m.set_router_strength(rho)
+        runs = [[t.clone() for t in m.run(x[i:i + n].contiguous())] for i in range(0, B, n)]
+        out.append([torch.cat(t) for t in zip(*runs)])
+        torch.cuda.synchronize()
+        m.close()
+    print(f"[rows] routers {routers} rho {rho}: tokens {out[0][2][0].tolist()}, "
+          f"{int((out[0][1] < cfg['L']).sum())} of {B} leave early", flush=True)
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
