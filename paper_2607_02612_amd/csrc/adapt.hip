@@ -59,7 +59,6 @@ template <int TMAX_, int WC_ = (TMAX_ <= 128 ? 4 : TMAX_ <= 256 ? 2 : 4)> struct
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
-static_assert(AdSize<AD_TMAX>::AMAX == AD_SIM_STRIDE, "similarity workspace stride");
 
 __device__ __forceinline__ int merge_count(float m, double rho, int r_b, int N, int rule) {
   // budget:   r = clamp(floor(((2 rho) m) r_b + 1/2), 0, floor(N/2));
@@ -523,8 +522,8 @@ __global__ __launch_bounds__(AD_NT) void adapt_kernel(AdaptArgs a) {
   if (!SIM && a.isM) {
     // best matches computed by similarity_kernel, one workgroup per pass
     for (int e = tid; e < nA; e += AD_NT) {
-      bestsim[e] = a.sim_v[(size_t)i * AD_SIM_STRIDE + e];
-      best[e] = a.sim_i[(size_t)i * AD_SIM_STRIDE + e];
+      bestsim[e] = a.sim_v[(base >> 1) + e];
+      best[e] = a.sim_i[(base >> 1) + e];
     }
   }
 
@@ -772,7 +771,8 @@ __global__ __launch_bounds__(AD_NT) void adapt_kernel(AdaptArgs a) {
 // sample, pass of SAG A rows): the same passes similarity_argmax makes one
 // after the other inside adapt_kernel, spread over workgroups so that a
 // small batch of long samples fills the GPU.  Results go to a.sim_v /
-// a.sim_i ([live sample][AMAX]); adapt_kernel reads them instead.
+// a.sim_i (a sample's floor(T / 2) A tokens from half its first packed row on);
+// adapt_kernel reads them instead.
 template <class Z>
 __global__ __launch_bounds__(AD_NT) void similarity_kernel(AdaptArgs a) {
   const int i = blockIdx.x, pass = blockIdx.y;
@@ -792,9 +792,8 @@ __global__ __launch_bounds__(AD_NT) void similarity_kernel(AdaptArgs a) {
   __shared__ int pbi[Z::WC * SAG];
   for (int t = threadIdx.x; t < T; t += AD_NT) prow[t] = a.rmap[base + t];
   __syncthreads();
-  similarity_argmax<Z>(a.x, prow, a.d, nA, nB, rn, a.sim_v + (size_t)i * AD_SIM_STRIDE,
-                       a.sim_i + (size_t)i * AD_SIM_STRIDE, Ahi, Alo, Bhi, Blo, pbv, pbi,
-                       pass * SAG, 1);
+  similarity_argmax<Z>(a.x, prow, a.d, nA, nB, rn, a.sim_v + (base >> 1), a.sim_i + (base >> 1),
+                       Ahi, Alo, Bhi, Blo, pbv, pbi, pass * SAG, 1);
 }
 
 hipError_t launch_adapt(const AdaptArgs& a, hipStream_t s) {

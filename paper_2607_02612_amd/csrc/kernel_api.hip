@@ -75,7 +75,7 @@ struct StepScratch {
   int* newlen;      // [B]
   int* r;           // [B]
   LiveCounts* cnt;  // nlive = B, M
-  float* sim_v;     // [B][AD_SIM_STRIDE] best matches of long samples
+  float* sim_v;     // [M / 2] best matches of long samples
   int* sim_i;
 };
 
@@ -84,7 +84,7 @@ struct StepScratch {
 size_t step_scratch_bytes(int B, int M, bool with_sim = false) {
   return align256((size_t)(B + 1) * 4) + 3 * align256((size_t)B * 4) +
          3 * align256((size_t)M * 4) + align256(sizeof(LiveCounts)) +
-         (with_sim ? 2 * align256((size_t)B * AD_SIM_STRIDE * 4) : 0);
+         (with_sim ? 2 * align256((size_t)(M / 2 + 1) * 4) : 0);
 }
 
 StepScratch carve(char* p, int B, int M, bool with_sim = false) {
@@ -102,8 +102,8 @@ StepScratch carve(char* p, int B, int M, bool with_sim = false) {
   s.size = (float*)take((size_t)M * 4);
   s.keep = (int*)take((size_t)M * 4);
   s.cnt = (LiveCounts*)take(sizeof(LiveCounts));
-  s.sim_v = with_sim ? (float*)take((size_t)B * AD_SIM_STRIDE * 4) : nullptr;
-  s.sim_i = with_sim ? (int*)take((size_t)B * AD_SIM_STRIDE * 4) : nullptr;
+  s.sim_v = with_sim ? (float*)take((size_t)(M / 2 + 1) * 4) : nullptr;
+  s.sim_i = with_sim ? (int*)take((size_t)(M / 2 + 1) * 4) : nullptr;
   return s;
 }
 

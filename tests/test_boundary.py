@@ -219,6 +219,13 @@ def test_workspace_entries_check_arguments_and_workspace_on_host():
                                                None, 1, None, None, None, br(po), ws, n, None) == code
 
 
+@pytest.mark.parametrize("batch,rows", [(1, 1), (256, 50432), (65536, 65536), (64, 36928)])
+def test_workspace_grows_with_rows_and_samples_only(batch, rows):
+    """16 bytes a row and as many a sample, each part rounded up to 256."""
+    n = _native.lib().fusion_test_workspace_bytes(batch, rows)
+    assert 0 < n <= 16 * rows + 16 * batch + 10 * 264
+
+
 def test_noalloc_merge_refuses_oversized_calls_on_host():
     """fusion_test_merge_noalloc returns FUSION_E_CAPACITY when a call would
     need more scratch than the static array holds, before any device call."""
