@@ -780,3 +780,34 @@ def test_workspace_entries_refuse_capture(torch_cuda):
         size.add_(0)
         with pytest.raises(FusionError):
             _kern().attention(qkv, size, [0, 4], 1)
+
+
+def test_calls_record_the_tensors_they_use(torch_cuda, monkeypatch):
+    """The calls return before their kernels ran, so each tensor of the caller
+    that they use is recorded on the stream: one that belongs to another stream
+    keeps its memory until then (gemm leaves that to the caller)."""
+    torch = torch_cuda
+    used = set()
+    record = torch.Tensor.record_stream
+    monkeypatch.setattr(torch.Tensor, "record_stream",
+                        lambda t, s: (used.add((t.data_ptr(), s.cuda_stream)), record(t, s))[1])
+    f = lambda *s: torch.rand(*s, device="cuda")
+    i32 = lambda *v: torch.tensor(v, dtype=torch.int32, device="cuda")
+    side = torch.cuda.Stream()
+    x, size, origin, qkv = f(5, 64), f(5) + 1, i32(0, 1, 2, 0, 1), f(5, 192)
+    scores, lg, ln = f(2, 1, 3), f(2, 7), (f(64), f(64))
+    pw, pb = f(64), f(1)
+    side.wait_stream(torch.cuda.current_stream())
+    cu, k = [0, 3, 5], _kern()
+    calls = [(lambda: k.attention(qkv, size, cu, 1), (qkv, size)),
+             (lambda: k.merge(x, size, origin, cu, [1, 0], 3), (x, size, origin)),
+             (lambda: k.merge(x, size, origin, cu, [1, 0], 3, noalloc=True), (x, size, origin)),
+             (lambda: k.topk_compact(x, size, origin, cu, 0.5, scores=scores, exit_logits=lg, delta=0.9,
+                                     ln=ln), (x, size, origin, scores, lg, *ln)),
+             (lambda: k.topk_compact(x, size, origin, cu, 0.5, prune_w=pw, prune_b=pb), (x, pw, pb))]
+    for n, (call, tensors) in enumerate(calls):
+        used.clear()
+        with torch.cuda.stream(side):
+            call()
+        assert {(t.data_ptr(), side.cuda_stream) for t in tensors} <= used, n
+    torch.cuda.synchronize()
