@@ -545,7 +545,7 @@ __global__ __launch_bounds__(MB / (32 * WR) * 128, MB == 128 ? 3 : 1) void gemm_
 // 16-byte chunks XOR-permuted by row % 8.  Row-map entries and residual rows
 // are fetched right after the ring's first loads.  The blocks follow the
 // dispatch order (a panel walk per XCD would leave XCDs idle here).
-template <int EPI, int WM, int WN, int NSTG, int NWV = WM * WN>
+template <int EPI, int WM, int WN, int NSTG, int NWV>
 __global__ __launch_bounds__(64 * NWV) void gemm_mfma_bf16_small(
     const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W, int N, int K,
     const int* M_dev, int M_host, Epi e) {
@@ -631,7 +631,7 @@ __global__ __launch_bounds__(64 * NWV) void gemm_mfma_bf16_small(
       wait_vm<DPW * (NSTG - 2)>();
     else
       wait_vm<0>();
-    if (NWV > 1) __syncthreads();
+    __syncthreads();
   };
   int sr = 0, sw = NSTG - 1;
   auto step = [&](int kt, int p) {
