@@ -689,7 +689,7 @@ __global__ __launch_bounds__(64 * NWV) void gemm_mfma_bf16_small(
 //     384 x 1536, 1092 blocks: two 17.4, four 15.5)
 //   up to small_tiles(): four blocks, which load each operand row for two
 //     (1576, 1152 x 384: 6.9 / 8.2 / 7.7 / 6.2; 2400, 768 x 3072: 35.6 / 41 / 37 / 26)
-//   beyond, the 64- and 128-row tiles (2400, 1152 x 384: 7.9 against 8.1)
+//   beyond, the medium kernel (2201, 1152 x 384: 7.7 against 8.6)
 template <int EPI>
 void launch_small(const bf16_t* A, int lda, const bf16_t* W, int N, int K, const int* M_dev,
                   int M_host, int M_ub, long t32, const Epi& e, hipStream_t s) {
