@@ -387,6 +387,27 @@ def test_attention_fp32_widths(torch_cuda, lengths, H, dh):
             assert np.abs(cls[i, :, :T] - P[:, 0]).max() <= tol, (shift, i)
             assert (cls[i, :, T:] == -1).all()
 
+
+@pytest.mark.parametrize("T", [65, 400, 640])
+def test_attention_fp32_sum_of_small_terms(torch_cuda, T):
+    """One key of weight 1 and T - 1 of weight 2^-25: summed one after the
+    other onto the 1 they vanish (5e-6 of the probability at 640 keys), summed
+    in pairs at most the few that meet it first do."""
+    torch = torch_cuda
+    print(f"[attention fp32 sum] T={T}", flush=True)
+    qkv = np.zeros((T, 192), np.float32)
+    qkv[0, 0] = 8.0  # times 1 / sqrt(64): the score is the key's first entry
+    qkv[1:, 64] = -25 * np.log(2.0)
+    _, cls = _kern().attention(torch.from_numpy(qkv).cuda(), torch.ones(T, device="cuda"), [0, T], 1,
+                               True, T)
+    S = qkv[:, 64].astype(np.float64)
+    P = np.exp(S) / np.exp(S).sum()
+    # 2 + 2 levels in a chunk of 64 keys, up to 10 chunks, 2 lane swaps, exp and
+    # the division: 16 roundings of half an ulp, and two of the exp's own
+    tol = 18 * 2.0 ** -24
+    assert np.abs(cls[0, 0].cpu().numpy() / P - 1).max() <= tol
+
+
 # ----------------------------------------------------------------- merge --
 def _tokens(rng, T, d, rank=8):
     """Hidden states with a low-rank structure (cosines spread over [-1, 1])."""
